@@ -98,9 +98,6 @@ ZFPX_HD uint64_t low_mask(int n) {  // n in [0, 64]
   return n >= 64 ? ~uint64_t(0) : ((uint64_t(1) << n) - 1);
 }
 
-// low_mask(n) for n in [1, 64] without a select: 2 << 63 wraps to 0.
-ZFPX_HD uint64_t mask_upto(int n) { return ((uint64_t)2 << (n - 1)) - 1; }
-
 ZFPX_HD int ctz64(uint64_t x) {  // x != 0
   return __builtin_ctzll(x);
 }
@@ -229,15 +226,16 @@ ZFPX_HD uint32_t bitop3(uint32_t s0, uint32_t s1, uint32_t s2) {
 #endif
 }
 
-// INV_HI complements the rows r + J written by the stage (the odd rows when
-// J = 1), at no cost.
+// The bit stages 4, 2 and 1 stay inside groups of eight rows: a points to the
+// first row of one group.  INV_HI complements the rows r + J written by the
+// stage (the odd rows when J = 1), at no cost.
 template <int J, uint32_t MASK, bool INV_HI = false>
 ZFPX_HD void transpose_bits64(uint64_t* a) {
   // Each half is shifted on its own: the bits a 64-bit shift would carry
   // across the halves land where the select mask discards them.
   constexpr uint32_t HM = MASK << J;
 #pragma unroll
-  for (int r = 0; r < 32; r++) {
+  for (int r = 0; r < 8; r++) {
     if ((r & J) == 0) {
       uint32_t xl = (uint32_t)a[r], xh = (uint32_t)(a[r] >> 32);
       uint32_t yl = (uint32_t)a[r + J], yh = (uint32_t)(a[r + J] >> 32);
@@ -253,7 +251,7 @@ ZFPX_HD void transpose_bits64(uint64_t* a) {
 ZFPX_HD void transpose_bits64_odd_in_inverted(uint64_t* a) {
   constexpr uint32_t M = 0x55555555u, HM = M << 1;
 #pragma unroll
-  for (int r = 0; r < 32; r += 2) {
+  for (int r = 0; r < 8; r += 2) {
     uint32_t xl = (uint32_t)a[r], xh = (uint32_t)(a[r] >> 32);
     uint32_t yl = (uint32_t)a[r + 1], yh = (uint32_t)(a[r + 1] >> 32);
     // odd row: (M & x >> 1) | (~M & ~y); even row: (HM & ~(y << 1)) | (~HM & x)
@@ -262,29 +260,55 @@ ZFPX_HD void transpose_bits64_odd_in_inverted(uint64_t* a) {
   }
 }
 
-// Each stage swaps one bit of the row index with the same bit of the column
-// index; the stages commute, so any order gives the transpose.
-// INVERT_ODD: afterwards rows 1, 3, ..., 31 are complemented.  XOR with a
-// constant commutes with the transpose, so the encoder's negabinary XOR with
-// 0xaaaaaaaa (bits 1, 3, ..., 31 of every coefficient) becomes exactly this.
-template <bool INVERT_ODD = false>
-ZFPX_HD void transpose32x2(uint64_t* a) {
-  transpose_bytes64<16>(a);
-  transpose_bytes64<8>(a);
-  transpose_bits64<4, 0x0f0f0f0fu>(a);
-  transpose_bits64<2, 0x33333333u>(a);
-  transpose_bits64<1, 0x55555555u, INVERT_ODD>(a);
+// Make N values available at this point (an empty asm that reads and writes
+// each).  Without it the compiler moves each output of a transpose stage to
+// its use behind the next branch: both inputs then stay live beside the
+// outputs already made, twice the registers.
+template <int N>
+ZFPX_HD void pin_values(uint64_t* a) {
+#if defined(__HIP_DEVICE_COMPILE__)
+#pragma unroll
+  for (int i = 0; i < N; i++) asm volatile("" : "+v"(a[i]));
+#else
+  (void)a;
+#endif
+}
+template <int N>
+ZFPX_HD void pin_values(int32_t* a) {
+#if defined(__HIP_DEVICE_COMPILE__)
+#pragma unroll
+  for (int i = 0; i < N; i++) asm volatile("" : "+v"(a[i]));
+#else
+  (void)a;
+#endif
 }
 
-// The transpose of rows 1, 3, ..., 31 complemented (the J = 1 stage first,
-// reading them inverted): for the decoder, whose odd bit planes are the
-// complemented ones (the negabinary XOR with 0xaaaaaaaa seen plane-wise).
-ZFPX_HD void transpose32x2_odd_in_inverted(uint64_t* a) {
+// Each stage swaps one bit of the row index with the same bit of the column
+// index; the stages commute, so any order gives the transpose.  It is done in
+// two parts: the byte stages over all rows, and the bit stages for each group
+// of eight rows (bit planes 8 g .. 8 g + 7), which the coder runs as it
+// reaches the group (and not at all for planes past the last one coded).
+ZFPX_HD void transpose_bytes(uint64_t* a) {
+  transpose_bytes64<16>(a);
+  transpose_bytes64<8>(a);
+}
+
+// Bit stages of a group, encoder: afterwards rows 1, 3, 5, 7 are complemented.
+// XOR with a constant commutes with the transpose, so the encoder's negabinary
+// XOR with 0xaaaaaaaa (the odd bits of every coefficient) becomes exactly this.
+ZFPX_HD void transpose_group(uint64_t* a) {
+  transpose_bits64<4, 0x0f0f0f0fu>(a);
+  transpose_bits64<2, 0x33333333u>(a);
+  transpose_bits64<1, 0x55555555u, true>(a);
+}
+
+// Bit stages of a group, decoder: of rows 1, 3, 5, 7 complemented (the J = 1
+// stage first, reading them inverted).  Eight zero rows become kZeroGroup.
+constexpr uint64_t kZeroGroup = 0xaaaaaaaaaaaaaaaaull;
+ZFPX_HD void transpose_group_odd_in_inverted(uint64_t* a) {
   transpose_bits64_odd_in_inverted(a);
   transpose_bits64<2, 0x33333333u>(a);
   transpose_bits64<4, 0x0f0f0f0fu>(a);
-  transpose_bytes64<8>(a);
-  transpose_bytes64<16>(a);
 }
 
 // ---------------------------------------------------------------------------
@@ -377,6 +401,105 @@ ZFPX_HD void pin_words(Words3& a) {
 #endif
 }
 
+// A value that is the same in every active lane, in a scalar register.
+ZFPX_HD int uniform_int(int x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_readfirstlane(x);
+#else
+  return x;
+#endif
+}
+
+// Any three-input bitwise function of 64-bit words (bitop3 on both halves).
+template <uint32_t TT>
+ZFPX_HD uint64_t bitop3_64(uint64_t s0, uint64_t s1, uint64_t s2) {
+  return (uint64_t)bitop3<TT>((uint32_t)s0, (uint32_t)s1, (uint32_t)s2) |
+         ((uint64_t)bitop3<TT>((uint32_t)(s0 >> 32), (uint32_t)(s1 >> 32), (uint32_t)(s2 >> 32))
+          << 32);
+}
+
+// (a << S) + b, one instruction for S <= 4 (opaque: the compiler would make
+// a multiply of two of them).
+template <int S>
+ZFPX_HD uint64_t shift_add64(uint64_t a, uint64_t b) {
+  uint64_t r = (a << S) + b;
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm("" : "+v"(r));
+#endif
+  return r;
+}
+
+// Population count of a 64-bit word.
+ZFPX_HD int popc64(uint64_t x) { return __builtin_popcountll(x); }
+
+// Whether any active lane of the wavefront holds a nonzero value (a scalar
+// branch: loops on it keep every lane, so their body must do nothing where
+// x = 0).
+ZFPX_HD bool any_lane(uint64_t x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_ballot_w64(x != 0) != 0;
+#else
+  return x != 0;
+#endif
+}
+
+// e without its lowest one.
+ZFPX_HD uint64_t drop_lowest(uint64_t e) { return e & (e - 1); }
+
+// Each one of y moved up by the number of ones below it (mod 2^64): y, plus
+// for t = 0, 1, ... y without its lowest t + 1 ones shifted up by t.  Steps
+// come in pairs (a step past a lane's last one adds nothing), the first with
+// constant shifts, which one shift-add instruction takes.
+ZFPX_HD uint64_t spread_ranks(uint64_t y) {
+  uint64_t sp = y, e = drop_lowest(y);
+  if (any_lane(e)) {
+    sp = shift_add64<0>(e, sp);
+    e = drop_lowest(e);
+    sp = shift_add64<1>(e, sp);
+    e = drop_lowest(e);
+    if (any_lane(e)) {
+      sp = shift_add64<2>(e, sp);
+      e = drop_lowest(e);
+      sp = shift_add64<3>(e, sp);
+      e = drop_lowest(e);
+      for (int t = 4; any_lane(e); t += 2) {
+        const int st = uniform_int(t);
+        sp += e << st;
+        e = drop_lowest(e);
+        sp += e << (st + 1);
+        e = drop_lowest(e);
+      }
+    }
+  }
+  return sp;
+}
+
+// Each one of y moved down by the number of ones below it: y, minus for
+// t = 1, 2, ... y without its lowest t ones shifted down by t.
+ZFPX_HD uint64_t gather_ranks(uint64_t y) {
+  uint64_t down = 0, e = drop_lowest(y);
+  if (any_lane(e)) {
+    down = e >> 1;
+    e = drop_lowest(e);
+    down += e >> 2;
+    e = drop_lowest(e);
+    if (any_lane(e)) {
+      down += e >> 3;
+      e = drop_lowest(e);
+      down += e >> 4;
+      e = drop_lowest(e);
+      for (int t = 5; any_lane(e); t += 2) {
+        const int st = uniform_int(t);
+        down += e >> st;
+        e = drop_lowest(e);
+        down += e >> (st + 1);
+        e = drop_lowest(e);
+      }
+    }
+  }
+  return y - down;
+}
+
 // ---------------------------------------------------------------------------
 // Encoder
 // ---------------------------------------------------------------------------
@@ -386,7 +509,20 @@ ZFPX_HD void pin_words(Words3& a) {
 // the slack words may receive bits past the budget and are not part of the
 // stream.  v is clobbered.  Returns the block's length in bits (at most
 // 64 * rate; 1 for a block coded as the single bit 0).
-template <int RATE>
+//
+// The coder is the larger half of the work and runs at the vector unit's issue
+// rate, so it is written for few instructions per bit plane:
+//  - a plane without newly significant coefficients in any lane is one mask,
+//    one OR into the slice and one compare: positions advance by `adv`, kept
+//    across planes and updated only when n changes;
+//  - bits may run past the budget into the slack words (a plane starts below
+//    the budget, so its verbatim bits end before bit maxbits + 63 and a code
+//    word of at most 64 bits stays in the two slack words): no test of the
+//    budget inside a plane;
+//  - the groups of a plane are one code word, also when they reach coefficient
+//    63; only a word of more than 64 bits takes the loop over groups.
+// VAR = false is fixed rate (every plane may be coded).
+template <int RATE, bool VAR = false>
 ZFPX_HD uint32_t encode_block(float* v, uint64_t* out, int rate_rt, int maxprec = 32,
                               int minexp = kMinExpNone) {
   const int rate = RATE > 0 ? RATE : rate_rt;
@@ -398,25 +534,27 @@ ZFPX_HD uint32_t encode_block(float* v, uint64_t* out, int rate_rt, int maxprec 
   uint32_t mx = f32_bits(amax);
   if (mx == 0) return 1;  // empty block: the single bit 0, all zero
   int emax = (int)(mx >> 23) - 126;  // subnormal maximum (field 0) gives -126
-  const int kmin = 32 - block_precision(emax, maxprec, minexp);
-  if (kmin == 32) return 1;  // no plane to code: the single bit 0
+  const int kmin = VAR ? 32 - block_precision(emax, maxprec, minexp) : 0;
+  if (VAR && kmin == 32) return 1;  // no plane to code: the single bit 0
   or_bits(out, 0, 1u | ((uint64_t)((emax + 127) & 0xff) << 1));
   // X[s] = coefficients s and 32+s (negabinary); after the transpose X[k] is
   // bit plane k: bit s of X[k] = bit k of coefficient s
   uint64_t X[32];
   {
     int32_t q[64];
-    if (emax >= -97) {
-      // 2^(30 - emax) is a normal float: one multiply per value is the same
-      // exact scaling (a product below 1 in magnitude truncates to 0 whatever
-      // its rounding)
-      const float sc = scale_pow2(1.0f, 30 - emax);
+    // 2^(30 - emax) is a normal float for emax >= -97: one multiply per value
+    // is the exact scaling (a product below 1 in magnitude truncates to 0
+    // whatever its rounding).  Smaller blocks are first scaled by 2^64,
+    // exactly: a step of its own, so that one cast and transform follows.
+    int sh = 30 - emax;
+    if (emax < -97) {
 #pragma unroll
-      for (int i = 0; i < 64; i++) q[i] = (int32_t)(v[i] * sc);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 64; i++) q[i] = (int32_t)scale_pow2(v[i], 30 - emax);
+      for (int i = 0; i < 64; i++) v[i] *= 0x1p64f;
+      sh -= 64;
     }
+    const float sc = scale_pow2(1.0f, sh);
+#pragma unroll
+    for (int i = 0; i < 64; i++) q[i] = (int32_t)(v[i] * sc);
     xform_fwd(q);
     // negabinary (q + mask) ^ mask: the add here, the XOR in the transpose
 #pragma unroll
@@ -427,62 +565,63 @@ ZFPX_HD uint32_t encode_block(float* v, uint64_t* out, int rate_rt, int maxprec 
     }
   }
   static_assert(kNegabinaryMask == 0xaaaaaaaau, "the transpose complements the odd planes");
-  transpose32x2<true>(X);
+  transpose_bytes(X);
+  pin_values<32>(X);
   uint32_t pos = 9;
-  int n = 0;
-  uint64_t vm = 0;  // low_mask(n), updated only when n changes
+  uint32_t n = 0;    // coefficients significant so far
+  uint32_t adv = 1;  // verbatim bits and a group test of 0: n + (n < 64)
+  uint64_t vm = 0;   // low_mask(n)
 #pragma unroll
-  for (int k = 31; k >= 0; k--) {
-    if (pos < maxbits && k >= kmin) {
-      const uint64_t x = X[k];
-      or_bits(out, pos, x & vm);  // the first n bits verbatim
-      pos += n;
-      // a bit at or above n (vm = 2^n - 1 with every bit below n set)
-      if (x > vm && pos < maxbits) {
-        uint64_t y = x >> n;  // bits not yet significant (n < 64 here)
-        // Each newly significant coefficient costs a group test 1, the zeros
-        // up to it and its own 1 (that one is implied, and not written, for
-        // coefficient 63).
-        bool done = false;
-        // Common case: all of the plane's groups fit one 64-bit code word and
-        // none reaches coefficient 63.  With the newly significant
-        // coefficients at positions q_0 < ... < q_(m-1) of y, the word has a
-        // group test 1 at bit 0 and, for each i, the coefficient's one at bit
-        // q_i + i + 1, followed (unless i is the last) by the next group test
-        // 1 at bit q_i + i + 2.  sp = sum_i 2^(q_i + i) (each one of y moved
-        // up by the number of ones below it) is built by adding, for t = 0,
-        // 1, ..., y without its lowest t + 1 ones shifted up by t.  The word
-        // is then written at once; groups that start past the budget only
-        // land in the slack words, and the budget is spent either way, so the
-        // coded bits are those of the group-by-group loop below.
-        const int hy = 63 - __builtin_clzll(y);           // q_(m-1)
-        const int hs = hy + __builtin_popcountll(y) - 1;  // its bit in sp
-        if (hs <= 62 && n + hy <= 62) {
-          uint64_t sp = y, e = y;
-          for (int t = 0;; t++) {
-            e &= e - 1;
-            if (e == 0) break;
-            sp += e << t;
+  for (int g = 3; g >= 0; g--) {
+    if (!any_lane(pos < maxbits && (!VAR || 8 * g + 7 >= kmin))) break;
+    transpose_group(X + 8 * g);
+    pin_values<8>(X + 8 * g);
+#pragma unroll
+    for (int k = 8 * g + 7; k >= 8 * g; k--) {
+      if (pos < maxbits && (!VAR || k >= kmin)) {
+        const uint64_t x = X[k];
+        or_bits(out, pos, x & vm);  // the first n bits verbatim
+        uint32_t gpos = pos + n;    // the group test
+        pos += adv;
+        if (x > vm) {  // a bit at or above n (so n < 64)
+          // Each newly significant coefficient costs a group test 1, the zeros
+          // up to it and its own 1 (that one is implied, and not written, for
+          // coefficient 63).  With the newly significant coefficients at
+          // positions q_0 < ... < q_(m-1) of y, the code word has a group test
+          // 1 at bit 0 and, for each i, the coefficient's one at bit
+          // q_i + i + 1, followed (unless i is the last) by the next group test
+          // 1 at bit q_i + i + 2.  With sp = sum_i 2^(q_i + i), whose top bit is
+          // hs, the word is 1 + 2 sp + 4 (sp - 2^hs): parts that share no bit.
+          uint64_t y = x >> n;
+          const uint32_t hx = 63u - (uint32_t)__builtin_clzll(x);  // coefficient of the last one
+          const uint32_t last = hx == 63 ? 1u : 0u;  // its one is implied
+          const uint32_t hs = hx - n + (uint32_t)popc64(y) - 1;
+          if (hs <= 62) {
+            // -2^(hs+2) for the group test that does not follow the last one,
+            // and -2^(hs+1) for its own one if implied
+            const uint64_t cut = (~(uint64_t)0 - 1 - last) << (hs + 1);
+            const uint64_t sp = spread_ranks(y);
+            or_bits(out, gpos, shift_add64<2>(sp, shift_add64<1>(sp, cut + 1)));
+            pos = gpos + hs + 3 - 2 * last;  // and the closing group test 0
+          } else {
+            // group by group, within the budget
+            uint32_t c = n;
+            pos = gpos;
+            while (y != 0 && pos < maxbits) {
+              const uint32_t p = (uint32_t)ctz64(y);
+              const uint32_t end = c + p == 63 ? 1u : 0u;
+              or_bits(out, pos, end ? uint64_t(1) : (uint64_t(1) | (uint64_t(2) << p)));
+              pos += p + 2 - end;
+              c += p + 1;
+              y = (y >> p) >> 1;
+            }
+            pos += 1 - last;
           }
-          // the three parts share no bit, so adds join them (shift-adds)
-          const uint64_t code = ((sp ^ (uint64_t(1) << hs)) << 2) + ((sp << 1) + 1);
-          or_bits(out, pos, code);
-          pos += (uint32_t)hs + 2;
-          n += hy + 1;
-          done = true;
+          n = hx + 1;
+          adv = hx < 62 ? hx + 2 : 64;
+          vm = ((uint64_t)2 << hx) - 1;
         }
-        while (!done && y != 0 && pos < maxbits) {
-          int p = ctz64(y);
-          int last = (n + p == 63);
-          uint64_t g = last ? uint64_t(1) : (uint64_t(1) | (uint64_t(2) << p));
-          or_bits(out, pos, g);
-          pos += p + 2 - last;
-          n += p + 1;
-          y = (y >> p) >> 1;
-        }
-        vm = mask_upto(n);
       }
-      pos += n < 64 ? 1 : 0;  // group test 0 (a zero bit)
     }
   }
   return pos < maxbits ? pos : maxbits;
@@ -492,9 +631,6 @@ ZFPX_HD uint32_t encode_block(float* v, uint64_t* out, int rate_rt, int maxprec 
 // Decoder
 // ---------------------------------------------------------------------------
 
-// Population count of a 64-bit word.
-ZFPX_HD int popc64(uint64_t x) { return __builtin_popcountll(x); }
-
 // The group tests and scans that follow a group test of 1, parsed from the
 // 64 stream bits v after it (bit 0 first), without a loop over the groups.
 // Each group is zeros up to a one (the newly significant coefficient), and
@@ -502,47 +638,40 @@ ZFPX_HD int popc64(uint64_t x) { return __builtin_popcountll(x); }
 // maximal run of ones that starts right after a zero (or at bit 0) the bits
 // alternate coefficient-one, group-test, coefficient-one, ...; a run that
 // ends on a coefficient-one is followed by the closing group test 0.
-// Returns the window position p of that last coefficient-one (64 if the
-// window holds none) and, through ev, the coefficient-ones at positions
-// 0..p.
-ZFPX_HD int parse_groups(uint64_t v, uint64_t& ev) {
+// Returns the coefficient-ones up to the first that a closing group test
+// follows, and through upto the mask of the bits up to it (all ones if the
+// window has none; bit 63 counts as followed by a 0).
+ZFPX_HD uint64_t parse_groups(uint64_t v, uint64_t& upto) {
   constexpr uint64_t kEven = 0x5555555555555555ull;
-  const uint64_t starts = v & ~(v << 1);
   // runs that start at an even position turn to zeros when their start bit
   // is added (the carry runs through them); the others are unchanged
-  const uint64_t t = v + (starts & kEven);
+  const uint64_t t = v + bitop3_64<0x40>(kEven, v, v << 1);  // v & ~(v << 1) & kEven
   // coefficient-ones: even positions of even-started runs, odd positions of
   // odd-started runs
-  const uint64_t e = v & (t ^ kEven);
+  const uint64_t e = bitop3_64<0x48>(kEven, v, t);  // v & (t ^ kEven)
   const uint64_t ends = e & ~(v >> 1);
-  if (ends == 0) {
-    ev = 0;
-    return 64;
-  }
-  const int p = ctz64(ends);
-  ev = e & (((uint64_t)2 << p) - 1);  // p <= 63: 2 << 63 wraps to 0, mask all ones
-  return p;
+  upto = ends ^ (ends - 1);
+  return e & upto;
 }
 
 // Decode the slice `in` (rate words followed by kSlackWords zero words) into
 // 64 floats (block-local order).
 //
-// Stream positions never pass maxbits (reads there return the zero slack,
-// which is what a budget that has run out yields for verbatim bits and group
-// tests).  Per bit plane: the verbatim bits are the window at pos masked to
-// the n significant coefficients, and the group test is bit n of the same
-// window; a plane whose group test is 0 (most of them) is done with that.
-// Otherwise the groups are parsed from the window after the group test
-// (parse_groups), unless the budget ends inside them or a scan could reach
-// coefficient 63 (whose one is implied, not coded): those take the
-// group-by-group loop.
-// TINY_SINGLE selects how results that may be subnormal (blocks with
-// emax < -95) are rounded: in single precision only, or from a double
-// product.  Both round once and agree bit for bit.  The choice changes how
-// the compiler lays out the whole decoder, not only that rare path: measured
-// on the 9.47 GB buffer, the variable-size decoder runs 6% faster with the
-// single-precision form and the fixed-rate decoders about 1% slower.
-template <int RATE, bool TINY_SINGLE = false>
+// Per bit plane the verbatim bits and the group test are the low n + 1 bits of
+// the window at pos: as a number they pass low_mask(n) exactly when the group
+// test is 1.  A plane whose group test is 0 (most of them) is done with that;
+// positions advance by `adv`, kept across planes and updated when n changes.
+// Reads past the budget return the zero slack, which is what a budget that
+// has run out yields for verbatim bits and group tests.
+// After a group test of 1 the groups are parsed from the window behind it
+// (parse_groups).  The run of groups ends, whichever comes first,
+//  - at a closing group test 0;
+//  - at coefficient 63, whose one is implied, not coded, with no test after;
+//  - at the end of the budget, where the coefficient that the scan has
+//    reached becomes significant.
+// A run that the window does not hold whole takes the loop over groups.
+// VAR = false is fixed rate (every plane may be coded).
+template <int RATE, bool VAR = false>
 ZFPX_HD void decode_block(const uint64_t* in, float* vout, int rate_rt, int maxprec = 32,
                           int minexp = kMinExpNone) {
   const int rate = RATE > 0 ? RATE : rate_rt;
@@ -557,74 +686,94 @@ ZFPX_HD void decode_block(const uint64_t* in, float* vout, int rate_rt, int maxp
   if (head & 1) {
     emax = (int)((head >> 1) & 0xff) - 127;
     pos = 9;
-    kmin = 32 - block_precision(emax, maxprec, minexp);
+    if (VAR) kmin = 32 - block_precision(emax, maxprec, minexp);
   }
   uint64_t X[32];  // bit planes, then (after the transpose) coefficients s, 32+s
-  int n = 0;
-  uint64_t vm = 0;  // low_mask(n)
+  uint32_t n = 0;     // coefficients significant so far
+  uint32_t adv = 1;   // verbatim bits and a group test of 0: n + (n < 64)
+  uint64_t vm = 0;    // low_mask(n)
+  uint64_t vm1 = 1;   // low_mask(min(n + 1, 64))
 #pragma unroll
-  for (int k = 31; k >= 0; k--) {
-    uint64_t x = 0;
-    if (k >= kmin && pos < maxbits) {
-      const uint64_t w = k == 31 ? window_of(wfirst, pos) : window64(in, pos);
-      x = w & vm;  // verbatim bits (zeros past the budget)
-      const uint32_t gpos = pos + (uint32_t)n;
-      const bool group = n < 64 && ((w >> (n & 63)) & 1) && gpos < maxbits;
-      pos = gpos + (n < 64 ? 1u : 0u);
-      if (group) {
-        // pos is the bit after the group test of 1
-        uint64_t ev;
-        const int p = parse_groups(window64(in, pos), ev);
-        const int m = popc64(ev);
-        const int last = n + p + 1 - m;  // coefficient of the last one found
-        // The whole run can be read off the window unless it reaches past
-        // it, past the budget, or up to the implied coefficient 63; then it
-        // is taken group by group (the second stage runs no step when the
-        // first applied: one stage after the other, not alternatives, keeps
-        // the compiler from carrying this block's planes through a loop
-        // around the decoder in extra registers).
-        const bool whole = p < 63 && pos + (uint32_t)p < maxbits && last <= 62;
-        if (whole) {
-          // each coefficient-one moves down by the number of group tests
-          // before it: y = ev - sum_t (ev without its lowest t ones) >> t
-          uint64_t y = ev, e = ev;
-          for (int t = 1;; t++) {
-            e &= e - 1;
-            if (e == 0) break;
-            y -= e >> t;
+  for (int g = 3; g >= 0; g--) {
+    if (!any_lane(pos < maxbits && (!VAR || 8 * g + 7 >= kmin))) {
+#pragma unroll
+      for (int k = 8 * g; k < 8 * g + 8; k++) X[k] = kZeroGroup;
+      continue;
+    }
+#pragma unroll
+    for (int k = 8 * g + 7; k >= 8 * g; k--) {
+      uint64_t x = 0;
+      if (pos < maxbits && (!VAR || k >= kmin)) {
+        const uint64_t w = k == 31 ? window_of(wfirst, pos) : window64(in, pos);
+        x = w & vm1;
+        pos += adv;
+        if (x > vm) {  // group test 1 (so n < 64); pos is the bit after it
+          x &= vm;
+          uint64_t upto;
+          const uint64_t ev = parse_groups(window64(in, pos), upto);
+          const uint32_t len = (uint32_t)popc64(upto);  // through the last one
+          uint64_t y = gather_ranks(ev);  // bit i: coefficient n + i
+          uint32_t hx = n + len - (uint32_t)popc64(ev);  // coefficient of the last one
+          uint32_t used = len + 1;                       // with the closing group test
+          uint32_t slow = 0;
+          if (len == 64 || hx > 62) {
+            // no closing group test before coefficient 63 or the window's end
+            const uint32_t left = maxbits - pos;  // budget behind the first test
+            const uint32_t d = 63 - n;
+            const uint64_t low = ((uint64_t)1 << d) - 1;
+            used = d + (uint32_t)popc64(y & low);  // bits that reach coefficient 63
+            if (used <= 64 && used <= left) {
+              y = (y & low) | (low + 1);
+              hx = 63;
+            } else if (left < 64) {
+              // all ones found lie within the budget
+              hx = n + left - (uint32_t)popc64(ev);
+              y |= (uint64_t)1 << (hx - n);
+              used = left;
+            } else {
+              slow = 1;
+              y = 0;
+              hx = n - 1;
+              used = 0;
+            }
           }
           x |= y << n;
-          n = last + 1;
-          pos += (uint32_t)p + 2;  // through the closing group test 0
-        }
-        // group by group: zeros up to the next one, at most up to
-        // coefficient 63 (implied) or the end of the budget
-        int g = whole ? 0 : 1;
-        while (g) {
-          int lim = 63 - n;
-          if ((int)(maxbits - pos) < lim) lim = (int)(maxbits - pos);
-          const uint64_t s = window64(in, pos);
-          const int z = s ? ctz64(s) : 64;
-          const int t = z < lim ? z : lim;
-          const int found = z < lim;
-          x |= uint64_t(1) << (n + t);
-          n += t + 1;
-          pos += (uint32_t)(t + found);
-          g = 0;
-          if (n < 64 && pos < maxbits) {
-            g = (int)((s >> (t + found)) & 1);  // t + found <= 63
-            pos += 1;
+          pos += used;
+          n = hx + 1;
+          // group by group: zeros up to the next one, at most up to
+          // coefficient 63 (implied) or the end of the budget (a second stage
+          // that runs no step when the first applied, not an alternative to it:
+          // the compiler would carry this block's planes through a loop around
+          // the decoder in extra registers)
+          while (slow) {
+            uint32_t lim = 63 - n;
+            if (maxbits - pos < lim) lim = maxbits - pos;
+            const uint64_t s = window64(in, pos);
+            const uint32_t z = s ? (uint32_t)ctz64(s) : 64;
+            const uint32_t t = z < lim ? z : lim;
+            const uint32_t found = z < lim ? 1u : 0u;
+            x |= uint64_t(1) << (n + t);
+            n += t + 1;
+            pos += t + found;
+            slow = 0;
+            if (n < 64 && pos < maxbits) {
+              slow = (uint32_t)((s >> (t + found)) & 1);  // t + found <= 63
+              pos += 1;
+            }
           }
+          vm = ((uint64_t)2 << (n - 1)) - 1;  // n >= 1 after a group test of 1
+          vm1 = shift_add64<1>(vm, 1);
+          adv = n < 63 ? n + 1 : 64;
         }
-        vm = mask_upto(n);  // n >= 1 after a group test of 1
       }
-      if (pos > maxbits) pos = maxbits;
+      X[k] = x;
     }
-    X[k] = x;
+    // odd planes complemented as the transpose reads them: every coefficient
+    // comes out XORed with the negabinary mask 0xaaaaaaaa (bits 1, 3, ..., 31)
+    transpose_group_odd_in_inverted(X + 8 * g);
+    pin_values<8>(X + 8 * g);
   }
-  // odd planes complemented as the transpose reads them: every coefficient
-  // comes out XORed with the negabinary mask 0xaaaaaaaa (bits 1, 3, ..., 31)
-  transpose32x2_odd_in_inverted(X);
+  transpose_bytes(X);
   int32_t q[64];
 #pragma unroll
   for (int s = 0; s < 32; s++) {
@@ -633,46 +782,41 @@ ZFPX_HD void decode_block(const uint64_t* in, float* vout, int rate_rt, int maxp
     q[kSeq.idx[32 + s]] = (int32_t)((uint32_t)(X[s] >> 32) - kNegabinaryMask);
   }
   xform_inv(q);
-  if (emax >= -95) {
-    // float(q) is one rounding and the power-of-two scale is exact (normal
-    // result); 2^(emax - 30) is a normal float, so a multiply applies it
-    const float sc = scale_pow2(1.0f, emax - 30);
-#pragma unroll
-    for (int i = 0; i < 64; i++) vout[i] = (float)q[i] * sc;
-  } else if (TINY_SINGLE) {
-    // Results may be subnormal; each is still rounded once, in single
-    // precision only.  With s = emax + 119 (in -7 .. 23),
-    // q * 2^(emax - 30) = q * 2^s * 2^-149, and 2^-149 is float32's smallest
-    // step.  A result of magnitude 2^-126 or more (|q| >= 2^(23 - s)) is
-    // normal: float(q), one rounding, then two exact power-of-two scalings.
-    // A smaller one is the integer nearest q * 2^s (ties to even; exact for
-    // s >= 0) times 2^-149, which float32 holds exactly; its sign is q's,
-    // zero included.
-    const int s = emax + 119;
-    const float up = scale_pow2(1.0f, emax + 34);  // 2^(emax - 30) = 2^-64 * up
+  pin_values<64>(q);
+  // Reconstruction is one rounding of q 2^(emax - 30): float(q), then a
+  // power-of-two scale that is exact.  It is exact also where the result is
+  // subnormal, as long as float32's smallest step 2^-149 is no more than one
+  // unit of q (emax >= -119): |q| < 2^23 there.  For smaller exponents the step
+  // is 2^k units, k = 1 .. 8, and q is first replaced, in place, by the result
+  // in units of 2^-149: a normal one (|q| >= 2^(23 + k)) is float(q) / 2^k, an
+  // integer; a subnormal one is q / 2^k rounded to the nearest integer (ties
+  // to even), and one that rounds to zero keeps q's sign.  Branches of the
+  // whole wavefront, on values replaced in place: with two alternative
+  // reconstructions the values of both would be live at once.
+  uint64_t minus_zero = 0;
+  if (any_lane(emax < -119)) {
+    const int k = emax < -119 ? -119 - emax : 0;
+    const uint32_t below = k > 0 ? 1u << (23 + k) : 0;
+    const uint32_t half = k > 0 ? 1u << (k - 1) : 1;
+    const float down = scale_pow2(1.0f, -k);
 #pragma unroll
     for (int i = 0; i < 64; i++) {
       const int32_t qi = q[i];
       const uint32_t mag = qi < 0 ? 0u - (uint32_t)qi : (uint32_t)qi;
-      float r;
-      if (mag >= (1u << (23 - s))) {
-        r = ((float)qi * 0x1p-64f) * up;
-      } else {
-        int32_t m;
-        if (s >= 0) {
-          m = (int32_t)((uint32_t)qi << s);
-        } else {
-          const int k = -s;
-          m = (qi + (1 << (k - 1)) - 1 + ((qi >> k) & 1)) >> k;  // |qi| < 2^30 here
-        }
-        r = __builtin_copysignf(((float)m * 0x1p-100f) * 0x1p-49f, qi < 0 ? -1.0f : 1.0f);
-      }
-      vout[i] = r;
+      const uint32_t rem = (uint32_t)qi & (2 * half - 1);  // |q| may reach 2^31 - 1: no carry past it
+      const int32_t sub = k > 0 ? (qi >> k) + (int32_t)((rem + half - 1 + ((qi >> k) & 1)) >> k) : 0;
+      const int32_t nor = k > 0 ? (int32_t)((float)qi * down) : qi;
+      q[i] = mag < below ? sub : nor;
+      minus_zero |= (uint64_t)(qi < 0 && q[i] == 0) << i;
+      pin_values<1>(q + i);
     }
-  } else {
-    // results may be subnormal: round once from the exact double product
+  }
+  const float sc = scale_pow2(1.0f, emax < -119 ? -149 : emax - 30);
 #pragma unroll
-    for (int i = 0; i < 64; i++) vout[i] = (float)__builtin_ldexp((double)q[i], emax - 30);
+  for (int i = 0; i < 64; i++) vout[i] = (float)q[i] * sc;
+  if (any_lane(minus_zero)) {
+#pragma unroll
+    for (int i = 0; i < 64; i++) vout[i] = (minus_zero >> i) & 1 ? -0.0f : vout[i];
   }
 }
 

@@ -493,6 +493,12 @@ __device__ __forceinline__ int opaque(int x) {
   return x;
 }
 
+// The lane number, computed anew: what is only needed again after the block
+// is coded holds no register meanwhile.
+__device__ __forceinline__ int lane_again() {
+  return __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, opaque(0)));
+}
+
 // One 64-block tile: gather + encode into the lane slices, then copy the
 // tile's words out (encode), or copy in + decode + scatter (decode).
 template <int RATE, bool VEC4, bool COH = false, class Geo>
@@ -532,13 +538,14 @@ __device__ __forceinline__ void decode_tile(const Geo& geo, const uint64_t* __re
   wave_sync_lds();
   if (lane < nact) {
     float val[64];
-    decode_block<RATE>(wlds + opaque(lane) * stride, val, rate);
+    decode_block<RATE>(wlds + lane * stride, val, rate);
+    const int l = lane_again();
     RunView run;
     if (!COH && geo.one_run(b0, nact, run)) {
-      scatter_run<VEC4>(dst, run, b0 + lane, val);
+      scatter_run<VEC4>(dst, run, b0 + l, val);
     } else {
       BlockView v;
-      geo.locate_tile(b0, lane, nact, v);
+      geo.locate_tile(b0, l, nact, v);
       scatter<VEC4, COH>(dst, v, val, vspan);
     }
   }
@@ -546,8 +553,14 @@ __device__ __forceinline__ void decode_tile(const Geo& geo, const uint64_t* __re
 
 // Workgroups cover the tiles of blocks [b_begin, b_end): one tile per
 // wavefront, or (PERSIST) a grid-stride loop over tiles.
+// Bound by vector instruction issue (93% of the issue slots taken on the
+// 9.47 GB buffer at rate 16; 2,909 vector instructions per tile and 2.80 ms,
+// from 3,407 and 3.21 ms with a loop over groups wherever coefficient 63 was
+// reached).  Four wavefronts per SIMD (at rate 16 as many as the LDS slices
+// allow) let instructions of two of them issue together more often than
+// three; five, possible at rate 8, are no faster.
 template <int RATE, bool VEC4, bool PERSIST, class Geo>
-__global__ __launch_bounds__(256) void k_encode(Geo geo, const float* __restrict__ src,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_encode(Geo geo, const float* __restrict__ src,
                                                 uint64_t* __restrict__ out, int rate_rt,
                                                 int32_t b_begin, int32_t b_end) {
   extern __shared__ uint64_t lds[];
@@ -583,12 +596,13 @@ __device__ __forceinline__ int32_t xcd_grouped(uint32_t i, uint32_t n) {
   return (int32_t)((k / kRun) * kGroup + x * kRun + k % kRun);
 }
 
-// The decoder's time is that of its writes (16 rows of 1 KB per tile): a
-// fourth wavefront per SIMD pays for the few registers it spills (three per
-// SIMD are slower), and its tiles are taken in XCD-grouped order, so that the
-// cache lines shared by neighbouring tiles are merged in one L2 rather than
-// written back in parts from two (the encoder, bound by instruction issue,
-// gains nothing from the order).
+// Bound by vector instruction issue (90% of the slots on the 9.47 GB buffer at
+// rate 16; 2,970 vector instructions per tile and 3.07 ms, from 3,545 and
+// 3.53 ms) with its writes close behind (16 row pieces of 1 KB per tile).  Four
+// wavefronts per SIMD hold the block without spilling; three are a fifth
+// slower.  Tiles are taken in XCD-grouped order, so that the cache lines
+// shared by neighbouring tiles are merged in one L2 rather than written back in
+// parts from two (the encoder gains nothing from the order).
 template <int RATE, bool VEC4, bool PERSIST, class Geo>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_decode(Geo geo, const uint64_t* __restrict__ in,
                                                 float* __restrict__ dst, int rate_rt,
@@ -663,7 +677,7 @@ __global__ __launch_bounds__(256) void k_encode_var(Geo geo, const float* __rest
     geo.locate_tile(b0, lane, nact, v);
     float val[64];
     gather<VEC4>(src, v, val);
-    bits = encode_block<CAP>(val, slice, cap, maxprec, minexp);
+    bits = encode_block<CAP, true>(val, slice, cap, maxprec, minexp);
   }
   const uint32_t nd = (bits + 31) >> 5;
   if (lane < nact) nd_out[b0 + lane] = (uint8_t)nd;
