@@ -293,13 +293,23 @@ ZFPX_HD void transpose_bytes(uint64_t* a) {
   transpose_bytes64<8>(a);
 }
 
-// Bit stages of a group, encoder: afterwards rows 1, 3, 5, 7 are complemented.
-// XOR with a constant commutes with the transpose, so the encoder's negabinary
-// XOR with 0xaaaaaaaa (the odd bits of every coefficient) becomes exactly this.
+// Bit stages of a group, encoder.  INVERT_ODD: afterwards rows 1, 3, 5, 7 are
+// complemented.  XOR with a constant commutes with the transpose, so the
+// encoder's negabinary XOR with 0xaaaaaaaa (the odd bits of every coefficient)
+// becomes exactly this.
+template <bool INVERT_ODD = false>
 ZFPX_HD void transpose_group(uint64_t* a) {
   transpose_bits64<4, 0x0f0f0f0fu>(a);
   transpose_bits64<2, 0x33333333u>(a);
-  transpose_bits64<1, 0x55555555u, true>(a);
+  transpose_bits64<1, 0x55555555u, INVERT_ODD>(a);
+}
+
+// The whole transpose at once.
+template <bool INVERT_ODD = false>
+ZFPX_HD void transpose32x2(uint64_t* a) {
+  transpose_bytes(a);
+#pragma unroll
+  for (int g = 0; g < 4; g++) transpose_group<INVERT_ODD>(a + 8 * g);
 }
 
 // Bit stages of a group, decoder: of rows 1, 3, 5, 7 complemented (the J = 1
@@ -574,7 +584,7 @@ ZFPX_HD uint32_t encode_block(float* v, uint64_t* out, int rate_rt, int maxprec 
 #pragma unroll
   for (int g = 3; g >= 0; g--) {
     if (!any_lane(pos < maxbits && (!VAR || 8 * g + 7 >= kmin))) break;
-    transpose_group(X + 8 * g);
+    transpose_group<true>(X + 8 * g);
     pin_values<8>(X + 8 * g);
 #pragma unroll
     for (int k = 8 * g + 7; k >= 8 * g; k--) {
