@@ -50,7 +50,6 @@ bool cfg_ok(LaunchCfg c, int rate) {
 struct zfpx_plan {
   int32_t nchunks = 0;
   int64_t nblocks = 0, nvalues = 0, min_elems = 0;
-  bool vec4 = true;
   std::vector<int64_t> chunk_blocks, chunk_first;  // host copies
   std::vector<int64_t> shape_key;                   // for the tuning cache
   SegDesc* d_segs = nullptr;
@@ -114,10 +113,6 @@ static int regular_setup(int64_t nx, int64_t ny, int64_t nz, int64_t sx, int64_t
   return ZFPX_OK;
 }
 
-static bool regular_vec4(const void* p, int64_t sx, int64_t sy, int64_t sz) {
-  return sx == 1 && (sy & 3) == 0 && (sz & 3) == 0 && aligned(p, 16);
-}
-
 int zfpx_encode_fixed_rate(const float* d_in, int64_t nx, int64_t ny, int64_t nz, int64_t sx,
                            int64_t sy, int64_t sz, int rate, void* d_out, size_t out_bytes,
                            void* stream) {
@@ -128,7 +123,7 @@ int zfpx_encode_fixed_rate(const float* d_in, int64_t nx, int64_t ny, int64_t nz
   if (nb == 0) return ZFPX_OK;
   if (!d_in || !d_out || !aligned(d_out, 8)) return ZFPX_EINVAL;
   if ((int64_t)out_bytes < nb * 8 * rate) return ZFPX_ENOSPC;
-  hipError_t e = launch_regular_encode(g, regular_vec4(d_in, sx, sy, sz), d_in, (uint64_t*)d_out,
+  hipError_t e = launch_regular_encode(g, sx == 1, d_in, (uint64_t*)d_out,
                                        rate, (int32_t)nb, default_cfg(kOpEncode, nb),
                                        (hipStream_t)stream);
   return e == hipSuccess ? ZFPX_OK : ZFPX_EHIP;
@@ -144,7 +139,7 @@ int zfpx_decode_fixed_rate(const void* d_in, size_t in_bytes, int64_t nx, int64_
   if (nb == 0) return ZFPX_OK;
   if (!d_in || !d_out || !aligned(d_in, 8)) return ZFPX_EINVAL;
   if ((int64_t)in_bytes < nb * 8 * rate) return ZFPX_ENOSPC;
-  hipError_t e = launch_regular_decode(g, regular_vec4(d_out, sx, sy, sz), (const uint64_t*)d_in,
+  hipError_t e = launch_regular_decode(g, sx == 1, (const uint64_t*)d_in,
                                        d_out, rate, (int32_t)nb, default_cfg(kOpDecode, nb),
                                        (hipStream_t)stream);
   return e == hipSuccess ? ZFPX_OK : ZFPX_EHIP;
@@ -181,20 +176,23 @@ int zfpx_plan_create(int32_t nchunks, const int64_t* chunk_base, const int64_t* 
   p->nblocks = t.nblocks;
   p->nvalues = t.nvalues;
   p->min_elems = t.min_elems;
-  p->vec4 = t.vec4;
   p->shape_key = {nchunks, t.nblocks, t.nvalues, (int64_t)t.segs.size()};
   const std::vector<SegDesc>& segs = t.segs;
   if (!segs.empty()) {
     const size_t nseg = segs.size();
+    // the device reads run starts eight at a time: eight more that no block
+    // reaches follow the table
+    std::vector<int32_t> starts = t.seg_block0;
+    starts.insert(starts.end(), 8, (int32_t)t.nblocks);
     if (hipMalloc(&p->d_segs, nseg * sizeof(SegDesc)) != hipSuccess ||
-        hipMalloc(&p->d_seg_block0, (nseg + 1) * sizeof(int32_t)) != hipSuccess ||
+        hipMalloc(&p->d_seg_block0, starts.size() * sizeof(int32_t)) != hipSuccess ||
         hipMalloc(&p->d_tile_seg, t.tile_seg.size() * sizeof(int32_t)) != hipSuccess) {
       zfpx_plan_destroy(p);
       return ZFPX_ENOMEM;
     }
     if (hipMemcpy(p->d_segs, segs.data(), nseg * sizeof(SegDesc), hipMemcpyHostToDevice) !=
             hipSuccess ||
-        hipMemcpy(p->d_seg_block0, t.seg_block0.data(), (nseg + 1) * sizeof(int32_t),
+        hipMemcpy(p->d_seg_block0, starts.data(), starts.size() * sizeof(int32_t),
                   hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(p->d_tile_seg, t.tile_seg.data(), t.tile_seg.size() * sizeof(int32_t),
                   hipMemcpyHostToDevice) != hipSuccess) {
@@ -257,8 +255,7 @@ static int do_pack_encode(const zfpx_plan* p, int32_t first, int32_t count, cons
   if (b1 == b0) return ZFPX_OK;
   if (!d_src || !d_send || !aligned(d_send, 8) || src_elems < p->min_elems) return ZFPX_EINVAL;
   if ((int64_t)send_bytes < p->nblocks * 8 * rate) return ZFPX_ENOSPC;
-  bool vec4 = p->vec4 && aligned(d_src, 16);
-  hipError_t e = launch_plan_encode(p->dev, vec4, d_src, (uint64_t*)d_send, rate, b0, b1,
+  hipError_t e = launch_plan_encode(p->dev, d_src, (uint64_t*)d_send, rate, b0, b1,
                                     p->config(kOpEncode, rate), (hipStream_t)stream);
   return e == hipSuccess ? ZFPX_OK : ZFPX_EHIP;
 }
@@ -273,8 +270,7 @@ static int do_decode_unpack(const zfpx_plan* p, int32_t first, int32_t count, co
   if (b1 == b0) return ZFPX_OK;
   if (!d_recv || !d_dst || !aligned(d_recv, 8) || dst_elems < p->min_elems) return ZFPX_EINVAL;
   if ((int64_t)recv_bytes < p->nblocks * 8 * rate) return ZFPX_ENOSPC;
-  bool vec4 = p->vec4 && aligned(d_dst, 16);
-  hipError_t e = launch_plan_decode(p->dev, vec4, (const uint64_t*)d_recv, d_dst, rate, b0, b1,
+  hipError_t e = launch_plan_decode(p->dev, (const uint64_t*)d_recv, d_dst, rate, b0, b1,
                                     p->config(kOpDecode, rate), (hipStream_t)stream);
   return e == hipSuccess ? ZFPX_OK : ZFPX_EHIP;
 }
@@ -456,9 +452,8 @@ int zfpx_plan_encode_var(const zfpx_plan* p, const float* d_src, int64_t src_ele
   const size_t stage = var_stage_words(p->nblocks, rate_cap);
   if (work_bytes < (stage + (size_t)(p->nblocks + 63) / 64) * sizeof(uint32_t))
     return ZFPX_ENOSPC;
-  bool vec4 = p->vec4 && aligned(d_src, 16);
   uint32_t* w = (uint32_t*)d_work;
-  hipError_t e = launch_plan_encode_var(p->dev, vec4, d_src, d_words, words_bytes / 4, d_nd,
+  hipError_t e = launch_plan_encode_var(p->dev, d_src, d_words, words_bytes / 4, d_nd,
                                         d_tile_off, w, w + stage, rate_cap, (int32_t)p->nblocks,
                                         maxprec, minexp, (hipStream_t)stream);
   return e == hipSuccess ? ZFPX_OK : ZFPX_EHIP;
@@ -489,8 +484,7 @@ int zfpx_plan_decode_var(const zfpx_plan* p, const uint32_t* d_words, size_t wor
   if (!d_words || !d_nd || !d_tile_off || !d_dst || !aligned(d_words, 4) ||
       !aligned(d_tile_off, 8) || dst_elems < p->min_elems)
     return ZFPX_EINVAL;
-  bool vec4 = p->vec4 && aligned(d_dst, 16);
-  hipError_t e = launch_plan_decode_var(p->dev, vec4, d_words, words_bytes / 4, d_nd, d_tile_off,
+  hipError_t e = launch_plan_decode_var(p->dev, d_words, words_bytes / 4, d_nd, d_tile_off,
                                         d_dst, rate_cap, (int32_t)p->nblocks, maxprec, minexp,
                                         (hipStream_t)stream);
   return e == hipSuccess ? ZFPX_OK : ZFPX_EHIP;

@@ -13,7 +13,7 @@ namespace zfpx {
 // Device-side view of a plan.
 struct PlanDev {
   const SegDesc* segs;
-  const int32_t* seg_block0;  // [nseg + 1], last entry = total blocks
+  const int32_t* seg_block0;  // [nseg + 9], the last 9 entries = total blocks
   const int32_t* tile_seg;    // [ntiles]: run holding block 64 * t
 };
 
@@ -40,27 +40,28 @@ struct LaunchCfg {
 constexpr int kOpEncode = 0;
 constexpr int kOpDecode = 1;
 
-// Launchers (kernels.hip).  Blocks [b_begin, b_end) of the geometry.
-hipError_t launch_plan_encode(const PlanDev& p, bool vec4, const float* src, uint64_t* out,
+// Launchers (kernels.hip).  Blocks [b_begin, b_end) of the geometry.  unit:
+// the array's x stride is 1 (a plan's always is).
+hipError_t launch_plan_encode(const PlanDev& p, const float* src, uint64_t* out,
                               int rate, int32_t b_begin, int32_t b_end, LaunchCfg cfg,
                               hipStream_t s);
-hipError_t launch_plan_decode(const PlanDev& p, bool vec4, const uint64_t* in, float* dst,
+hipError_t launch_plan_decode(const PlanDev& p, const uint64_t* in, float* dst,
                               int rate, int32_t b_begin, int32_t b_end, LaunchCfg cfg,
                               hipStream_t s);
-hipError_t launch_regular_encode(const RegularDev& g, bool vec4, const float* src,
+hipError_t launch_regular_encode(const RegularDev& g, bool unit, const float* src,
                                  uint64_t* out, int rate, int32_t nblocks, LaunchCfg cfg,
                                  hipStream_t s);
-hipError_t launch_regular_decode(const RegularDev& g, bool vec4, const uint64_t* in, float* dst,
+hipError_t launch_regular_decode(const RegularDev& g, bool unit, const uint64_t* in, float* dst,
                                  int rate, int32_t nblocks, LaunchCfg cfg, hipStream_t s);
 // Variable-size modes over a whole plan: the encoder's scratch is a staging
 // area of var_stage_words 32-bit words plus one count per tile.
 size_t var_stage_words(int64_t nblocks, int cap);
 hipError_t launch_fill_u64(uint64_t* p, int64_t n, uint64_t v, hipStream_t s);
-hipError_t launch_plan_encode_var(const PlanDev& p, bool vec4, const float* src, uint32_t* out,
+hipError_t launch_plan_encode_var(const PlanDev& p, const float* src, uint32_t* out,
                                   uint64_t out_words, uint8_t* nd, int64_t* tile_off,
                                   uint32_t* stage, uint32_t* tile_count, int cap,
                                   int32_t nblocks, int maxprec, int minexp, hipStream_t s);
-hipError_t launch_plan_decode_var(const PlanDev& p, bool vec4, const uint32_t* in,
+hipError_t launch_plan_decode_var(const PlanDev& p, const uint32_t* in,
                                   uint64_t in_words, const uint8_t* nd, const int64_t* tile_off,
                                   float* dst, int cap, int32_t nblocks, int maxprec, int minexp,
                                   hipStream_t s);

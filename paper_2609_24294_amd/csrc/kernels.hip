@@ -21,6 +21,12 @@
 namespace zfpx {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+// Pieces of a row, which start at any element: a vector memory instruction
+// takes any 4-byte address, so rows off a 16-byte boundary move in 16-byte
+// pieces too (a 45 x 426 x 853 array at rate 16, encoded and decoded, takes
+// 83 us; 95 with such rows read and written element by element).
+typedef float f32x4_row __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x2_row __attribute__((ext_vector_type(2), aligned(4)));
 
 // ---------------------------------------------------------------------------
 // Block location
@@ -74,11 +80,22 @@ struct PlanGeo {
     r.minlen = min(min(r.rlen[0], r.rlen[1]), min(r.rlen[2], r.rlen[3]));
     return true;
   }
-  // Any block: find its run from the run table.
-  __device__ __forceinline__ void locate(int32_t b, BlockView& v) const {
-    int32_t s = p.tile_seg[b >> 6];
-    while (p.seg_block0[s + 1] <= b) s++;
-    const SegDesc& d = p.segs[s];
+  // Block b of a tile that starts in run s: the run starts after s are read
+  // eight at a time with scalar loads, and the lane's run is s plus the number
+  // of them at or below b (the table ends in eight entries that no block
+  // reaches).
+  __device__ __forceinline__ void locate(int32_t s, int32_t b, BlockView& v) const {
+    int32_t run = s;
+    for (;;) {
+      int32_t at[8];
+#pragma unroll
+      for (int i = 0; i < 8; i++) at[i] = uniform_load(p.seg_block0, s + 1 + i);
+#pragma unroll
+      for (int i = 0; i < 8; i++) run += at[i] <= b ? 1 : 0;
+      if (!any_lane(at[7] <= b)) break;
+      s += 8;
+    }
+    const SegDesc& d = p.segs[run];
 #pragma unroll
     for (int i = 0; i < 4; i++) {
       v.rbase[i] = d.rbase[i];
@@ -93,7 +110,7 @@ struct PlanGeo {
   // Block b0 + lane of a tile whose first block b0 is the same on every lane
   // and whose last active block is b0 + nact - 1.  A tile that meets at most
   // two runs reads both descriptors with scalar loads and each lane picks
-  // its own; other tiles look every block up.
+  // its own; in other tiles each lane reads the descriptor of its run.
   __device__ __forceinline__ void locate_tile(int32_t b0, int lane, int nact,
                                               BlockView& v) const {
     int32_t s = uniform_load(p.tile_seg, b0 >> 6);
@@ -102,7 +119,7 @@ struct PlanGeo {
     const int32_t e1 = uniform_load(p.seg_block0, s + 1);
     // e1 <= last < total blocks, so run s + 1 exists and so does entry s + 2
     if (e1 <= last && uniform_load(p.seg_block0, s + 2) <= last) {
-      locate(b0 + lane, v);
+      locate(s, b0 + lane, v);
       return;
     }
     const int32_t b = b0 + lane;
@@ -131,14 +148,26 @@ struct PlanGeo {
 
 struct RegularGeo {
   RegularDev g;
-  __device__ __forceinline__ void locate(int32_t b, BlockView& v) const {
-    uint32_t ub = (uint32_t)b;
-    uint32_t t = ub / (uint32_t)g.nbx;
-    uint32_t bx = ub - t * (uint32_t)g.nbx;
-    uint32_t bz = t / (uint32_t)g.nby;
-    uint32_t by = t - bz * (uint32_t)g.nby;
-    int64_t y0 = 4 * (int64_t)by, z0 = 4 * (int64_t)bz;
-    int64_t zoff = z0 * g.sz;
+  // u / d for u < d + 64: at most one row further where d >= 64; below, an
+  // exact multiply (u < 128).
+  static __device__ __forceinline__ uint32_t wraps(uint32_t u, uint32_t d) {
+    if (d >= 64) return u >= d ? 1u : 0u;
+    return (u * ((65536u + d - 1) / d)) >> 16;
+  }
+  // Block b0 + lane: the divisions are those of the wave-uniform b0.
+  __device__ __forceinline__ void locate_tile(int32_t b0, int lane, int, BlockView& v) const {
+    const uint32_t t0 = (uint32_t)b0 / (uint32_t)g.nbx;
+    uint32_t bx = (uint32_t)b0 - t0 * (uint32_t)g.nbx + (uint32_t)lane;
+    uint32_t bz = t0 / (uint32_t)g.nby;
+    uint32_t by = t0 - bz * (uint32_t)g.nby;
+    const uint32_t rows = wraps(bx, (uint32_t)g.nbx);
+    bx -= rows * (uint32_t)g.nbx;
+    by += rows;
+    const uint32_t planes = wraps(by, (uint32_t)g.nby);
+    by -= planes * (uint32_t)g.nby;
+    bz += planes;
+    const int64_t y0 = 4 * (int64_t)by, z0 = 4 * (int64_t)bz;
+    const int64_t zoff = z0 * g.sz;
 #pragma unroll
     for (int i = 0; i < 4; i++) {
       int64_t y = y0 + i < g.ny ? y0 + i : g.ny - 1;
@@ -151,10 +180,27 @@ struct RegularGeo {
     v.nrow = (int32_t)(g.ny - y0 < 4 ? g.ny - y0 : 4);
     v.x0 = (int32_t)(4 * bx);
   }
-  __device__ __forceinline__ void locate_tile(int32_t b0, int lane, int, BlockView& v) const {
-    locate(b0 + lane, v);
+  // A tile within one row of blocks (every tile but those at row ends): the
+  // same view as a plan's run.  Rows of fewer blocks than a tile have none.
+  __device__ __forceinline__ bool one_run(int32_t b0, int nact, RunView& r) const {
+    if (nact > g.nbx) return false;
+    const uint32_t t = (uint32_t)b0 / (uint32_t)g.nbx;
+    const uint32_t bx0 = (uint32_t)b0 - t * (uint32_t)g.nbx;
+    if (bx0 + (uint32_t)nact > (uint32_t)g.nbx) return false;
+    const uint32_t bz = t / (uint32_t)g.nby;
+    const int64_t y0 = 4 * (int64_t)(t - bz * (uint32_t)g.nby), z0 = 4 * (int64_t)bz;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      r.rbase[i] = z0 * g.sz + (y0 + i < g.ny ? y0 + i : g.ny - 1) * g.sy;
+      r.rlen[i] = (int32_t)g.nx;
+    }
+    r.lstride = g.sz;
+    r.nlev = (int32_t)(g.nz - z0 < 4 ? g.nz - z0 : 4);
+    r.nrow = (int32_t)(g.ny - y0 < 4 ? g.ny - y0 : 4);
+    r.block0 = b0 - (int32_t)bx0;
+    r.minlen = (int32_t)g.nx;
+    return true;
   }
-  __device__ __forceinline__ bool one_run(int32_t, int, RunView&) const { return false; }
 };
 
 // COH: system-coherent element accesses that bypass the (per-XCD) L2, used by
@@ -185,11 +231,30 @@ __device__ __forceinline__ bool whole_block(const BlockView& v) {
   return v.nlev == 4 && v.nrow == 4 && v.sx == 1 && v.x0 + 3 < len;
 }
 
-// Gather the 64 values of a block.  A whole block takes sixteen 16-byte
+// Element dx of a row's piece that was read `shift` points early (so as not to
+// pass the row's end): positions past the end repeat the last point.
+__device__ __forceinline__ void shift_piece(float* o, int shift) {
+  float a = o[0], b = o[1], c = o[2];
+  const float d = o[3];
+#pragma unroll
+  for (int i = 0; i < 3; i++) {
+    const bool move = shift > i;
+    a = move ? b : a;
+    b = move ? c : b;
+    c = move ? d : c;
+  }
+  o[0] = a;
+  o[1] = b;
+  o[2] = c;
+}
+
+// Gather the 64 values of a block with unit x stride (UNIT): sixteen 16-byte
 // loads with no branch between them, so that all of them are in flight at
-// once; any other block loads every element from its clamped position
-// (repeating the last level, row or point), also without branches.
-template <bool VEC4, bool COH = false>
+// once.  Missing levels repeat the last one; a piece that would pass its row's
+// end is read at the row's last four points and shifted in registers.  Tiles
+// with a row of fewer than four points, and other strides, load every element
+// from its clamped position.
+template <bool UNIT, bool COH = false>
 __device__ __forceinline__ void gather(const float* __restrict__ src, const BlockView& v,
                                        float* val, uint32_t vspan = 0) {
   if (COH && vspan != 0 && whole_block(v)) {
@@ -210,20 +275,35 @@ __device__ __forceinline__ void gather(const float* __restrict__ src, const Bloc
     }
     return;
   }
-  if (VEC4 && !COH && whole_block(v)) {
-#pragma unroll
-    for (int dz = 0; dz < 4; dz++) {
+  if (UNIT && !COH) {
+    const int minlen = min(min(v.rlen[0], v.rlen[1]), min(v.rlen[2], v.rlen[3]));
+    if (!any_lane(minlen < 4)) {
+      int early[4];
+      const float* row[4];
 #pragma unroll
       for (int dy = 0; dy < 4; dy++) {
-        f32x4 f = *reinterpret_cast<const f32x4*>(src + v.rbase[dy] + dz * v.lstride + v.x0);
-        float* o = val + 16 * dz + 4 * dy;
-        o[0] = f.x;
-        o[1] = f.y;
-        o[2] = f.z;
-        o[3] = f.w;
+        early[dy] = max(0, v.x0 - (v.rlen[dy] - 4));
+        row[dy] = src + v.rbase[dy] + (v.x0 - early[dy]);
       }
+#pragma unroll
+      for (int dz = 0; dz < 4; dz++) {
+#pragma unroll
+        for (int dy = 0; dy < 4; dy++) {
+          const f32x4_row f = *reinterpret_cast<const f32x4_row*>(row[dy]);
+          float* o = val + 16 * dz + 4 * dy;
+          o[0] = f.x;
+          o[1] = f.y;
+          o[2] = f.z;
+          o[3] = f.w;
+          row[dy] += dz + 1 < v.nlev ? v.lstride : 0;
+        }
+      }
+      if (any_lane(early[0] | early[1] | early[2] | early[3])) {
+#pragma unroll
+        for (int i = 0; i < 16; i++) shift_piece(val + 4 * i, early[i & 3]);
+      }
+      return;
     }
-    return;
   }
 #pragma unroll
   for (int dz = 0; dz < 4; dz++) {
@@ -242,8 +322,25 @@ __device__ __forceinline__ void gather(const float* __restrict__ src, const Bloc
   }
 }
 
-// NT: whole blocks are stored with the non-temporal hint.
-template <bool VEC4, bool COH = false, bool NT = false>
+// A row's piece: 16 bytes, or the row's last one to three points in pieces of
+// eight and four bytes.  NT: the 16-byte stores carry the non-temporal hint.
+template <bool NT>
+__device__ __forceinline__ void store_piece(float* q, const float* o, int left) {
+  if (left >= 4) {
+    const f32x4_row f = {o[0], o[1], o[2], o[3]};
+    if (NT)
+      __builtin_nontemporal_store(f, reinterpret_cast<f32x4_row*>(q));
+    else
+      *reinterpret_cast<f32x4_row*>(q) = f;
+  } else if (left > 0) {
+    const float a = o[0], c = o[2];
+    if (left >= 2) *reinterpret_cast<f32x2_row*>(q) = f32x2_row{a, o[1]};
+    if (left & 1) q[left - 1] = left == 1 ? a : c;
+  }
+}
+
+// NT: whole pieces are stored with the non-temporal hint.
+template <bool UNIT, bool COH = false, bool NT = false>
 __device__ __forceinline__ void scatter(float* __restrict__ dst, const BlockView& v,
                                         const float* val, uint32_t vspan = 0) {
   if (COH && vspan != 0 && whole_block(v)) {
@@ -261,18 +358,32 @@ __device__ __forceinline__ void scatter(float* __restrict__ dst, const BlockView
     }
     return;
   }
-  if (VEC4 && !COH && whole_block(v)) {
+  if (UNIT && !COH) {
+    float* row[4];
+    int left[4];  // points of the row from x0 on (none for a row that is not there)
+#pragma unroll
+    for (int dy = 0; dy < 4; dy++) {
+      row[dy] = dst + v.rbase[dy] + v.x0;
+      left[dy] = dy < v.nrow ? v.rlen[dy] - v.x0 : 0;
+    }
+    const bool whole = v.nlev == 4 && min(min(left[0], left[1]), min(left[2], left[3])) >= 4;
+    if (!any_lane(!whole)) {
+#pragma unroll
+      for (int dz = 0; dz < 4; dz++) {
+#pragma unroll
+        for (int dy = 0; dy < 4; dy++) {
+          store_piece<NT>(row[dy], val + 16 * dz + 4 * dy, 4);
+          row[dy] += v.lstride;
+        }
+      }
+      return;
+    }
 #pragma unroll
     for (int dz = 0; dz < 4; dz++) {
 #pragma unroll
       for (int dy = 0; dy < 4; dy++) {
-        const float* o = val + 16 * dz + 4 * dy;
-        f32x4 f = {o[0], o[1], o[2], o[3]};
-        f32x4* q = reinterpret_cast<f32x4*>(dst + v.rbase[dy] + dz * v.lstride + v.x0);
-        if (NT)
-          __builtin_nontemporal_store(f, q);
-        else
-          *q = f;
+        store_piece<NT>(row[dy], val + 16 * dz + 4 * dy, dz < v.nlev ? left[dy] : 0);
+        row[dy] += v.lstride;
       }
     }
     return;
@@ -287,40 +398,50 @@ __device__ __forceinline__ void scatter(float* __restrict__ dst, const BlockView
           int64_t base = v.rbase[dy] + zoff;
           int len = v.rlen[dy];
           const float* o = val + 16 * dz + 4 * dy;
-          if (VEC4 && !COH && v.x0 + 3 < len) {
-            f32x4 f = {o[0], o[1], o[2], o[3]};
-            *reinterpret_cast<f32x4*>(dst + base + v.x0) = f;
-          } else {
 #pragma unroll
-            for (int dx = 0; dx < 4; dx++)
-              if (v.x0 + dx < len) {
-                if (COH)
-                  coh_store(dst + base + (int64_t)(v.x0 + dx) * v.sx, o[dx]);
-                else
-                  dst[base + (int64_t)(v.x0 + dx) * v.sx] = o[dx];
-              }
-          }
+          for (int dx = 0; dx < 4; dx++)
+            if (v.x0 + dx < len) {
+              if (COH)
+                coh_store(dst + base + (int64_t)(v.x0 + dx) * v.sx, o[dx]);
+              else
+                dst[base + (int64_t)(v.x0 + dx) * v.sx] = o[dx];
+            }
         }
       }
     }
   }
 }
 
-// Block b of a one-run tile: whole blocks load sixteen 16-byte pieces at a
-// scalar row address plus the lane's x offset; others take the clamped
-// element path of gather().
-template <bool VEC4>
+// The same as a block view, for the tiles of a run that are not whole.
+__device__ __forceinline__ BlockView run_block(const RunView& r, int32_t x0) {
+  BlockView v;
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    v.rbase[i] = r.rbase[i];
+    v.rlen[i] = r.rlen[i];
+  }
+  v.lstride = r.lstride;
+  v.sx = 1;
+  v.nlev = r.nlev;
+  v.nrow = r.nrow;
+  v.x0 = x0;
+  return v;
+}
+
+// Block b of a one-run tile.  If every block of the tile is whole: sixteen
+// 16-byte pieces at a scalar row address plus the lane's x offset.
 __device__ __forceinline__ void gather_run(const float* __restrict__ src, const RunView& r,
                                            int32_t b, float* val) {
   const int32_t x0 = 4 * (b - r.block0);
-  if (VEC4 && r.nlev == 4 && r.nrow == 4 && x0 + 3 < r.minlen) {
+  if (r.nlev == 4 && !any_lane(x0 + 3 >= r.minlen)) {
 #pragma unroll
     for (int dz = 0; dz < 4; dz++) {
 #pragma unroll
       for (int dy = 0; dy < 4; dy++) {
         const float* row = src + (r.rbase[dy] + dz * r.lstride);
         // read once: a streaming (non-temporal) load
-        f32x4 f = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(row + (uint32_t)x0));
+        const f32x4_row f =
+            __builtin_nontemporal_load(reinterpret_cast<const f32x4_row*>(row + (uint32_t)x0));
         float* o = val + 16 * dz + 4 * dy;
         o[0] = f.x;
         o[1] = f.y;
@@ -330,49 +451,26 @@ __device__ __forceinline__ void gather_run(const float* __restrict__ src, const 
     }
     return;
   }
-  BlockView v;
-#pragma unroll
-  for (int i = 0; i < 4; i++) {
-    v.rbase[i] = r.rbase[i];
-    v.rlen[i] = r.rlen[i];
-  }
-  v.lstride = r.lstride;
-  v.sx = 1;
-  v.nlev = r.nlev;
-  v.nrow = r.nrow;
-  v.x0 = x0;
-  gather<false>(src, v, val);
+  gather<true>(src, run_block(r, x0), val);
 }
 
-template <bool VEC4>
 __device__ __forceinline__ void scatter_run(float* __restrict__ dst, const RunView& r, int32_t b,
                                             const float* val) {
   const int32_t x0 = 4 * (b - r.block0);
-  if (VEC4 && r.nlev == 4 && r.nrow == 4 && x0 + 3 < r.minlen) {
+  if (r.nlev == 4 && r.nrow == 4 && !any_lane(x0 + 3 >= r.minlen)) {
 #pragma unroll
     for (int dz = 0; dz < 4; dz++) {
 #pragma unroll
       for (int dy = 0; dy < 4; dy++) {
         float* row = dst + (r.rbase[dy] + dz * r.lstride);
         const float* o = val + 16 * dz + 4 * dy;
-        f32x4 f = {o[0], o[1], o[2], o[3]};
-        *reinterpret_cast<f32x4*>(row + (uint32_t)x0) = f;
+        const f32x4_row f = {o[0], o[1], o[2], o[3]};
+        *reinterpret_cast<f32x4_row*>(row + (uint32_t)x0) = f;
       }
     }
     return;
   }
-  BlockView v;
-#pragma unroll
-  for (int i = 0; i < 4; i++) {
-    v.rbase[i] = r.rbase[i];
-    v.rlen[i] = r.rlen[i];
-  }
-  v.lstride = r.lstride;
-  v.sx = 1;
-  v.nlev = r.nlev;
-  v.nrow = r.nrow;
-  v.x0 = x0;
-  scatter<VEC4>(dst, v, val);
+  scatter<true>(dst, run_block(r, x0), val);
 }
 
 // Make loaded values available at this point (an empty asm that reads and
@@ -501,7 +599,7 @@ __device__ __forceinline__ int lane_again() {
 
 // One 64-block tile: gather + encode into the lane slices, then copy the
 // tile's words out (encode), or copy in + decode + scatter (decode).
-template <int RATE, bool VEC4, bool COH = false, class Geo>
+template <int RATE, bool UNIT, bool COH = false, class Geo>
 __device__ __forceinline__ void encode_tile(const Geo& geo, const float* __restrict__ src,
                                             uint64_t* __restrict__ out, int rate, int lane,
                                             uint64_t* wlds, int32_t b0, int nact,
@@ -510,15 +608,15 @@ __device__ __forceinline__ void encode_tile(const Geo& geo, const float* __restr
   uint64_t* slice = wlds + lane * stride;
   for (int i = 0; i < stride; i++) slice[i] = 0;
   RunView run;
-  const bool uniform = !COH && geo.one_run(b0, nact, run);
+  const bool uniform = UNIT && !COH && geo.one_run(b0, nact, run);
   if (lane < nact) {
     float val[64];
     if (uniform) {
-      gather_run<VEC4>(src, run, b0 + lane, val);
+      gather_run(src, run, b0 + lane, val);
     } else {
       BlockView v;
       geo.locate_tile(b0, lane, nact, v);
-      gather<VEC4, COH>(src, v, val, vspan);
+      gather<UNIT, COH>(src, v, val, vspan);
     }
     encode_block<RATE>(val, slice, rate);
   }
@@ -526,7 +624,7 @@ __device__ __forceinline__ void encode_tile(const Geo& geo, const float* __restr
   copy_tile<RATE, true, COH>(out + (int64_t)b0 * rate, wlds, opaque(lane), nact, rate);
 }
 
-template <int RATE, bool VEC4, bool COH = false, class Geo>
+template <int RATE, bool UNIT, bool COH = false, class Geo>
 __device__ __forceinline__ void decode_tile(const Geo& geo, const uint64_t* __restrict__ in,
                                             float* __restrict__ dst, int rate, int lane,
                                             uint64_t* wlds, int32_t b0, int nact,
@@ -541,12 +639,12 @@ __device__ __forceinline__ void decode_tile(const Geo& geo, const uint64_t* __re
     decode_block<RATE>(wlds + lane * stride, val, rate);
     const int l = lane_again();
     RunView run;
-    if (!COH && geo.one_run(b0, nact, run)) {
-      scatter_run<VEC4>(dst, run, b0 + l, val);
+    if (UNIT && !COH && geo.one_run(b0, nact, run)) {
+      scatter_run(dst, run, b0 + l, val);
     } else {
       BlockView v;
       geo.locate_tile(b0, l, nact, v);
-      scatter<VEC4, COH>(dst, v, val, vspan);
+      scatter<UNIT, COH>(dst, v, val, vspan);
     }
   }
 }
@@ -559,7 +657,7 @@ __device__ __forceinline__ void decode_tile(const Geo& geo, const uint64_t* __re
 // reached).  Four wavefronts per SIMD (at rate 16 as many as the LDS slices
 // allow) let instructions of two of them issue together more often than
 // three; five, possible at rate 8, are no faster.
-template <int RATE, bool VEC4, bool PERSIST, class Geo>
+template <int RATE, bool UNIT, bool PERSIST, class Geo>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_encode(Geo geo, const float* __restrict__ src,
                                                 uint64_t* __restrict__ out, int rate_rt,
                                                 int32_t b_begin, int32_t b_end) {
@@ -575,7 +673,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   for (;;) {
     const int32_t b0 = b_begin + (t << 6);
     const int nact = b_end - b0 < 64 ? b_end - b0 : 64;
-    encode_tile<RATE, VEC4>(geo, src, out, rate, opaque(lane), wlds, b0, nact);
+    encode_tile<RATE, UNIT>(geo, src, out, rate, opaque(lane), wlds, b0, nact);
     if (!PERSIST) break;
     t += gridDim.x * waves;
     if (t >= ntiles) break;
@@ -603,7 +701,7 @@ __device__ __forceinline__ int32_t xcd_grouped(uint32_t i, uint32_t n) {
 // slower.  Tiles are taken in XCD-grouped order, so that the cache lines
 // shared by neighbouring tiles are merged in one L2 rather than written back in
 // parts from two (the encoder gains nothing from the order).
-template <int RATE, bool VEC4, bool PERSIST, class Geo>
+template <int RATE, bool UNIT, bool PERSIST, class Geo>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_decode(Geo geo, const uint64_t* __restrict__ in,
                                                 float* __restrict__ dst, int rate_rt,
                                                 int32_t b_begin, int32_t b_end) {
@@ -619,7 +717,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   for (;;) {
     const int32_t b0 = b_begin + (t << 6);
     const int nact = b_end - b0 < 64 ? b_end - b0 : 64;
-    decode_tile<RATE, VEC4>(geo, in, dst, rate, opaque(lane), wlds, b0, nact);
+    decode_tile<RATE, UNIT>(geo, in, dst, rate, opaque(lane), wlds, b0, nact);
     if (!PERSIST) break;
     t += gridDim.x * waves;
     if (t >= ntiles) break;
@@ -651,7 +749,7 @@ __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x, int lane) {
   return x;
 }
 
-template <int CAP, bool VEC4, class Geo>
+template <int CAP, class Geo>
 __global__ __launch_bounds__(256) void k_encode_var(Geo geo, const float* __restrict__ src,
                                                     uint32_t* __restrict__ stage,
                                                     uint32_t* __restrict__ tile_count,
@@ -676,7 +774,7 @@ __global__ __launch_bounds__(256) void k_encode_var(Geo geo, const float* __rest
     BlockView v;
     geo.locate_tile(b0, lane, nact, v);
     float val[64];
-    gather<VEC4>(src, v, val);
+    gather<true>(src, v, val);
     bits = encode_block<CAP, true>(val, slice, cap, maxprec, minexp);
   }
   const uint32_t nd = (bits + 31) >> 5;
@@ -840,7 +938,7 @@ __global__ __launch_bounds__(256) void k_var_place(const uint32_t* __restrict__ 
 
 // Any content of the stream, counts and offsets decodes without a fault:
 // counts are clamped to the cap and words outside the stream read as zero.
-template <int CAP, bool VEC4, class Geo>
+template <int CAP, class Geo>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_decode_var(
     Geo geo, const uint32_t* __restrict__ in, uint64_t in_words, const uint8_t* __restrict__ nd_in,
     const int64_t* __restrict__ tile_off, float* __restrict__ dst, int cap_rt, int32_t nblocks,
@@ -888,7 +986,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     geo.locate_tile(b0, lane, nact, v);
     // streaming stores: 9% faster here on a 9.47 GB output; the fixed-rate
     // decoders gain nothing from them
-    scatter<VEC4, false, true>(dst, v, val);
+    scatter<true, false, true>(dst, v, val);
   }
 }
 
@@ -1388,31 +1486,31 @@ static dim3 grid_for(int32_t nblocks, LaunchCfg cfg, bool* persistent) {
   return dim3((unsigned)(g > 0 ? g : 1));
 }
 
-#define ZFPX_RATE_SWITCH2(KERNEL, GEO, VEC4, PERSIST, ...)                                \
+#define ZFPX_RATE_SWITCH2(KERNEL, GEO, UNIT, PERSIST, ...)                                \
   switch (rate) {                                                                          \
     case 8:                                                                                \
-      hipLaunchKernelGGL((KERNEL<8, VEC4, PERSIST, GEO>), grid, block, shm, s, __VA_ARGS__); \
+      hipLaunchKernelGGL((KERNEL<8, UNIT, PERSIST, GEO>), grid, block, shm, s, __VA_ARGS__); \
       break;                                                                               \
     case 16:                                                                               \
-      hipLaunchKernelGGL((KERNEL<16, VEC4, PERSIST, GEO>), grid, block, shm, s, __VA_ARGS__); \
+      hipLaunchKernelGGL((KERNEL<16, UNIT, PERSIST, GEO>), grid, block, shm, s, __VA_ARGS__); \
       break;                                                                               \
     case 32:                                                                               \
-      hipLaunchKernelGGL((KERNEL<32, VEC4, PERSIST, GEO>), grid, block, shm, s, __VA_ARGS__); \
+      hipLaunchKernelGGL((KERNEL<32, UNIT, PERSIST, GEO>), grid, block, shm, s, __VA_ARGS__); \
       break;                                                                               \
     default:                                                                               \
-      hipLaunchKernelGGL((KERNEL<0, VEC4, PERSIST, GEO>), grid, block, shm, s, __VA_ARGS__); \
+      hipLaunchKernelGGL((KERNEL<0, UNIT, PERSIST, GEO>), grid, block, shm, s, __VA_ARGS__); \
       break;                                                                               \
   }
 
 // One tile per wavefront unless the configuration asks for a persistent grid.
-#define ZFPX_RATE_SWITCH(KERNEL, GEO, VEC4, ...)                                         \
+#define ZFPX_RATE_SWITCH(KERNEL, GEO, UNIT, ...)                                         \
   if (persistent) {                                                                        \
-    ZFPX_RATE_SWITCH2(KERNEL, GEO, VEC4, true, __VA_ARGS__)                                \
+    ZFPX_RATE_SWITCH2(KERNEL, GEO, UNIT, true, __VA_ARGS__)                                \
   } else {                                                                                 \
-    ZFPX_RATE_SWITCH2(KERNEL, GEO, VEC4, false, __VA_ARGS__)                               \
+    ZFPX_RATE_SWITCH2(KERNEL, GEO, UNIT, false, __VA_ARGS__)                               \
   }
 
-hipError_t launch_plan_encode(const PlanDev& p, bool vec4, const float* src, uint64_t* out,
+hipError_t launch_plan_encode(const PlanDev& p, const float* src, uint64_t* out,
                               int rate, int32_t b_begin, int32_t b_end, LaunchCfg cfg,
                               hipStream_t s) {
   if (b_end <= b_begin) return hipSuccess;
@@ -1420,15 +1518,11 @@ hipError_t launch_plan_encode(const PlanDev& p, bool vec4, const float* src, uin
   dim3 grid = grid_for(b_end - b_begin, cfg, &persistent), block(cfg.wg);
   size_t shm = lds_bytes(cfg.wg, rate);
   PlanGeo geo{p};
-  if (vec4) {
-    ZFPX_RATE_SWITCH(k_encode, PlanGeo, true, geo, src, out, rate, b_begin, b_end);
-  } else {
-    ZFPX_RATE_SWITCH(k_encode, PlanGeo, false, geo, src, out, rate, b_begin, b_end);
-  }
+  ZFPX_RATE_SWITCH(k_encode, PlanGeo, true, geo, src, out, rate, b_begin, b_end);
   return hipGetLastError();
 }
 
-hipError_t launch_plan_decode(const PlanDev& p, bool vec4, const uint64_t* in, float* dst,
+hipError_t launch_plan_decode(const PlanDev& p, const uint64_t* in, float* dst,
                               int rate, int32_t b_begin, int32_t b_end, LaunchCfg cfg,
                               hipStream_t s) {
   if (b_end <= b_begin) return hipSuccess;
@@ -1436,15 +1530,11 @@ hipError_t launch_plan_decode(const PlanDev& p, bool vec4, const uint64_t* in, f
   dim3 grid = grid_for(b_end - b_begin, cfg, &persistent), block(cfg.wg);
   size_t shm = lds_bytes(cfg.wg, rate);
   PlanGeo geo{p};
-  if (vec4) {
-    ZFPX_RATE_SWITCH(k_decode, PlanGeo, true, geo, in, dst, rate, b_begin, b_end);
-  } else {
-    ZFPX_RATE_SWITCH(k_decode, PlanGeo, false, geo, in, dst, rate, b_begin, b_end);
-  }
+  ZFPX_RATE_SWITCH(k_decode, PlanGeo, true, geo, in, dst, rate, b_begin, b_end);
   return hipGetLastError();
 }
 
-hipError_t launch_regular_encode(const RegularDev& g, bool vec4, const float* src,
+hipError_t launch_regular_encode(const RegularDev& g, bool unit, const float* src,
                                  uint64_t* out, int rate, int32_t nblocks, LaunchCfg cfg,
                                  hipStream_t s) {
   if (nblocks <= 0) return hipSuccess;
@@ -1453,7 +1543,7 @@ hipError_t launch_regular_encode(const RegularDev& g, bool vec4, const float* sr
   size_t shm = lds_bytes(cfg.wg, rate);
   RegularGeo geo{g};
   int32_t b0 = 0;
-  if (vec4) {
+  if (unit) {
     ZFPX_RATE_SWITCH(k_encode, RegularGeo, true, geo, src, out, rate, b0, nblocks);
   } else {
     ZFPX_RATE_SWITCH(k_encode, RegularGeo, false, geo, src, out, rate, b0, nblocks);
@@ -1461,7 +1551,7 @@ hipError_t launch_regular_encode(const RegularDev& g, bool vec4, const float* sr
   return hipGetLastError();
 }
 
-hipError_t launch_regular_decode(const RegularDev& g, bool vec4, const uint64_t* in, float* dst,
+hipError_t launch_regular_decode(const RegularDev& g, bool unit, const uint64_t* in, float* dst,
                                  int rate, int32_t nblocks, LaunchCfg cfg, hipStream_t s) {
   if (nblocks <= 0) return hipSuccess;
   bool persistent;
@@ -1469,7 +1559,7 @@ hipError_t launch_regular_decode(const RegularDev& g, bool vec4, const uint64_t*
   size_t shm = lds_bytes(cfg.wg, rate);
   RegularGeo geo{g};
   int32_t b0 = 0;
-  if (vec4) {
+  if (unit) {
     ZFPX_RATE_SWITCH(k_decode, RegularGeo, true, geo, in, dst, rate, b0, nblocks);
   } else {
     ZFPX_RATE_SWITCH(k_decode, RegularGeo, false, geo, in, dst, rate, b0, nblocks);
@@ -1531,19 +1621,19 @@ hipError_t launch_f16_restore(const uint16_t* in, size_t n, float* out, hipStrea
   return hipGetLastError();
 }
 
-#define ZFPX_CAP_SWITCH(KERNEL, GEO, VEC4, ...)                                     \
+#define ZFPX_CAP_SWITCH(KERNEL, GEO, ...)                                     \
   switch (cap) {                                                                   \
     case 8:                                                                        \
-      hipLaunchKernelGGL((KERNEL<8, VEC4, GEO>), grid, block, shm, s, __VA_ARGS__);  \
+      hipLaunchKernelGGL((KERNEL<8, GEO>), grid, block, shm, s, __VA_ARGS__);  \
       break;                                                                       \
     case 16:                                                                       \
-      hipLaunchKernelGGL((KERNEL<16, VEC4, GEO>), grid, block, shm, s, __VA_ARGS__); \
+      hipLaunchKernelGGL((KERNEL<16, GEO>), grid, block, shm, s, __VA_ARGS__); \
       break;                                                                       \
     case 32:                                                                       \
-      hipLaunchKernelGGL((KERNEL<32, VEC4, GEO>), grid, block, shm, s, __VA_ARGS__); \
+      hipLaunchKernelGGL((KERNEL<32, GEO>), grid, block, shm, s, __VA_ARGS__); \
       break;                                                                       \
     default:                                                                       \
-      hipLaunchKernelGGL((KERNEL<0, VEC4, GEO>), grid, block, shm, s, __VA_ARGS__);  \
+      hipLaunchKernelGGL((KERNEL<0, GEO>), grid, block, shm, s, __VA_ARGS__);  \
       break;                                                                       \
   }
 
@@ -1558,7 +1648,7 @@ hipError_t launch_fill_u64(uint64_t* p, int64_t n, uint64_t v, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_plan_encode_var(const PlanDev& p, bool vec4, const float* src, uint32_t* out,
+hipError_t launch_plan_encode_var(const PlanDev& p, const float* src, uint32_t* out,
                                   uint64_t out_words, uint8_t* nd, int64_t* tile_off,
                                   uint32_t* stage, uint32_t* tile_count, int cap,
                                   int32_t nblocks, int maxprec, int minexp, hipStream_t s) {
@@ -1568,13 +1658,8 @@ hipError_t launch_plan_encode_var(const PlanDev& p, bool vec4, const float* src,
   dim3 grid((ntiles + wg / 64 - 1) / (wg / 64)), block(wg);
   size_t shm = lds_bytes(wg, cap);
   PlanGeo geo{p};
-  if (vec4) {
-    ZFPX_CAP_SWITCH(k_encode_var, PlanGeo, true, geo, src, stage, tile_count, nd, cap, nblocks,
+  ZFPX_CAP_SWITCH(k_encode_var, PlanGeo, geo, src, stage, tile_count, nd, cap, nblocks,
                     maxprec, minexp);
-  } else {
-    ZFPX_CAP_SWITCH(k_encode_var, PlanGeo, false, geo, src, stage, tile_count, nd, cap, nblocks,
-                    maxprec, minexp);
-  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int32_t nchunks = (int32_t)(((int64_t)ntiles + kScanChunk - 1) / kScanChunk);
@@ -1592,7 +1677,7 @@ hipError_t launch_plan_encode_var(const PlanDev& p, bool vec4, const float* src,
   return hipGetLastError();
 }
 
-hipError_t launch_plan_decode_var(const PlanDev& p, bool vec4, const uint32_t* in,
+hipError_t launch_plan_decode_var(const PlanDev& p, const uint32_t* in,
                                   uint64_t in_words, const uint8_t* nd, const int64_t* tile_off,
                                   float* dst, int cap, int32_t nblocks, int maxprec, int minexp,
                                   hipStream_t s) {
@@ -1602,13 +1687,8 @@ hipError_t launch_plan_decode_var(const PlanDev& p, bool vec4, const uint32_t* i
   dim3 grid((ntiles + wg / 64 - 1) / (wg / 64)), block(wg);
   size_t shm = lds_bytes(wg, cap);
   PlanGeo geo{p};
-  if (vec4) {
-    ZFPX_CAP_SWITCH(k_decode_var, PlanGeo, true, geo, in, in_words, nd, tile_off, dst, cap,
+  ZFPX_CAP_SWITCH(k_decode_var, PlanGeo, geo, in, in_words, nd, tile_off, dst, cap,
                     nblocks, maxprec, minexp);
-  } else {
-    ZFPX_CAP_SWITCH(k_decode_var, PlanGeo, false, geo, in, in_words, nd, tile_off, dst, cap,
-                    nblocks, maxprec, minexp);
-  }
   return hipGetLastError();
 }
 

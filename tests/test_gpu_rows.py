@@ -1,0 +1,86 @@
+"""Row pieces at any alignment and length, tiles over many runs, and row
+widths around a tile: GPU against the CPU oracle, bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2609_24294_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+NAN = np.float32(np.nan)
+
+
+def _u64(t):
+    return t.cpu().numpy().view(np.uint64)
+
+
+def _bits(a):
+    return np.asarray(a, np.float32).view(np.uint32)
+
+
+def _ragged(rng, nchunks, longest):
+    """Chunks of 1..9 levels and 1..11 rows of 1..longest points, every row and
+    level at an element offset of its own, disjoint."""
+    base, stride, levels, rs, offs, lens = [], [], [], [0], [], []
+    at = int(rng.integers(0, 4))
+    for _ in range(nchunks):
+        nrow, nlev = int(rng.integers(1, 12)), int(rng.integers(1, 10))
+        ln = rng.integers(1, longest + 1, nrow)
+        o = np.cumsum(ln + rng.integers(0, 3, nrow)) - ln
+        span = int(o[-1] + ln[-1] + rng.integers(0, 4))
+        base.append(at)
+        stride.append(span)
+        levels.append(nlev)
+        offs.append(o)
+        lens.append(ln)
+        rs.append(rs[-1] + nrow)
+        at += span * nlev + int(rng.integers(0, 4))
+    return W.ChunkSet(np.array(base), np.array(stride), np.array(levels), np.array(rs),
+                      np.concatenate(offs), np.concatenate(lens), at)
+
+
+@pytest.mark.parametrize("longest,nchunks", [(3, 60), (9, 60), (70, 40), (700, 6)])
+def test_ragged_rows(zfpx_lib, longest, nchunks):
+    rng = np.random.default_rng(longest)
+    cs = _ragged(rng, nchunks, longest)
+    src = (100 + np.cumsum(rng.standard_normal(cs.buffer_elems)) / 8).astype(np.float32)
+    plan = zfpx_lib.Plan.from_chunkset(cs)
+    # one element off a 16-byte boundary
+    room = torch.zeros(src.size + 1, device=DEV)
+    room[1:] = torch.from_numpy(src)
+    for rate in (5, 8, 16):
+        send = zfpx_lib.zfpx_pack_encode(plan, room[1:], rate)
+        want = oracle.pack_encode(cs, src, rate)
+        assert np.array_equal(_u64(send), want), rate
+        out = torch.full((src.size + 1,), float("nan"), device=DEV)
+        zfpx_lib.zfpx_decode_unpack(plan, send, rate, out[1:])
+        back = np.full(src.size, NAN)
+        oracle.decode_unpack(cs, want, rate, back)
+        assert np.array_equal(_bits(out[1:].cpu()), _bits(back)), rate
+    words, nd, off = zfpx_lib.zfpx_plan_encode_var(plan, room[1:], 20, zfpx_lib.MINEXP_NONE, 16)
+    w, n, o = oracle.pack_encode_var(cs, src, 20, zfpx_lib.MINEXP_NONE, 16)
+    assert np.array_equal(off.cpu().numpy(), o) and np.array_equal(nd.cpu().numpy(), n)
+    assert np.array_equal(words.cpu().numpy().view(np.uint32)[: o[-1]], w)
+    out = torch.full((src.size + 1,), float("nan"), device=DEV)
+    zfpx_lib.zfpx_plan_decode_var(plan, words, nd, off, 20, zfpx_lib.MINEXP_NONE, 16, out[1:])
+    back = np.full(src.size, NAN)
+    oracle.decode_unpack_var(cs, w, n, 20, zfpx_lib.MINEXP_NONE, 16, back)
+    assert np.array_equal(_bits(out[1:].cpu()), _bits(back))
+
+
+@pytest.mark.parametrize("nx", [1, 3, 5, 61, 252, 255, 256, 257, 260, 515, 1027])
+@pytest.mark.parametrize("nz,ny", [(1, 1), (5, 3), (8, 70), (3, 300)])
+def test_row_widths_around_a_tile(zfpx_lib, nx, nz, ny):
+    rng = np.random.default_rng(nx * ny + nz)
+    a = np.cumsum(rng.standard_normal((nz, ny, nx)), 2).astype(np.float32)
+    d = torch.from_numpy(a).to(DEV)
+    for rate in (8, 11):
+        words = zfpx_lib.zfpx_encode_fixed_rate(d, rate)
+        want = oracle.encode_regular(a, rate)
+        assert np.array_equal(_u64(words), want), rate
+        out = torch.full_like(d, float("nan"))
+        zfpx_lib.zfpx_decode_fixed_rate(words, rate, out)
+        assert np.array_equal(_bits(out.cpu()), _bits(oracle.decode_regular(want, a.shape, rate)))
