@@ -540,20 +540,30 @@ __device__ __forceinline__ void copy_tile(uint64_t* __restrict__ g, uint64_t* ld
       }
     }
   } else {
+    // Any other rate: word w of the tile lies in block w / rate.  A lane's
+    // words are 64 apart, so its slice address moves on by a fixed step, plus
+    // one more block where the word index within the block passes the rate.
+    // Four words per lane per round, all read before any is waited for (reads
+    // past the end repeat word 0 and are not stored).
     const int rate = RATE > 0 ? RATE : rate_rt;
     const int stride = (rate + kSlackWords) | 1;
     const int nw = nact * rate;
-    // four words per lane per round, all read before any is waited for
-    // (reads past the end repeat word 0 and are not stored)
+    const int blocks = 64 / rate, over = 64 - blocks * rate;
+    int idx = lane % rate;
+    int slot = lane / rate * stride + idx;
     for (int w0 = lane; w0 < nw; w0 += 256) {
       uint64_t v[4];
       int at[4];
 #pragma unroll
       for (int j = 0; j < 4; j++) {
-        const int w = w0 + 64 * j < nw ? w0 + 64 * j : 0;
-        const int blk = w / rate;
-        at[j] = blk * stride + (w - blk * rate);
-        v[j] = TO_GLOBAL ? lds[at[j]] : gload64<COH>(g + w);
+        const int w = w0 + 64 * j;
+        at[j] = w < nw ? slot : 0;
+        v[j] = TO_GLOBAL ? lds[at[j]] : gload64<COH>(g + (w < nw ? w : 0));
+        idx += over;
+        slot += blocks * stride + over;
+        const bool wrap = idx >= rate;
+        idx -= wrap ? rate : 0;
+        slot += wrap ? stride - rate : 0;
       }
       pin_words64(v);
 #pragma unroll
