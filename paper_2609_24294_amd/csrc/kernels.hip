@@ -323,15 +323,14 @@ __device__ __forceinline__ void gather(const float* __restrict__ src, const Bloc
 }
 
 // A row's piece: 16 bytes, or the row's last one to three points in pieces of
-// eight and four bytes.  NT: the 16-byte stores carry the non-temporal hint.
-template <bool NT>
+// eight and four bytes.  The 16-byte stores are streaming (non-temporal): every
+// byte is written once.  Rows of short runs gain most (decoding the
+// Fourier-space share at rate 12, 320-byte pieces: 38.0 against 48.0 us), other
+// shapes 0 to 4%.
 __device__ __forceinline__ void store_piece(float* q, const float* o, int left) {
   if (left >= 4) {
     const f32x4_row f = {o[0], o[1], o[2], o[3]};
-    if (NT)
-      __builtin_nontemporal_store(f, reinterpret_cast<f32x4_row*>(q));
-    else
-      *reinterpret_cast<f32x4_row*>(q) = f;
+    __builtin_nontemporal_store(f, reinterpret_cast<f32x4_row*>(q));
   } else if (left > 0) {
     const float a = o[0], c = o[2];
     if (left >= 2) *reinterpret_cast<f32x2_row*>(q) = f32x2_row{a, o[1]};
@@ -339,8 +338,7 @@ __device__ __forceinline__ void store_piece(float* q, const float* o, int left) 
   }
 }
 
-// NT: whole pieces are stored with the non-temporal hint.
-template <bool UNIT, bool COH = false, bool NT = false>
+template <bool UNIT, bool COH = false>
 __device__ __forceinline__ void scatter(float* __restrict__ dst, const BlockView& v,
                                         const float* val, uint32_t vspan = 0) {
   if (COH && vspan != 0 && whole_block(v)) {
@@ -372,7 +370,7 @@ __device__ __forceinline__ void scatter(float* __restrict__ dst, const BlockView
       for (int dz = 0; dz < 4; dz++) {
 #pragma unroll
         for (int dy = 0; dy < 4; dy++) {
-          store_piece<NT>(row[dy], val + 16 * dz + 4 * dy, 4);
+          store_piece(row[dy], val + 16 * dz + 4 * dy, 4);
           row[dy] += v.lstride;
         }
       }
@@ -382,7 +380,7 @@ __device__ __forceinline__ void scatter(float* __restrict__ dst, const BlockView
     for (int dz = 0; dz < 4; dz++) {
 #pragma unroll
       for (int dy = 0; dy < 4; dy++) {
-        store_piece<NT>(row[dy], val + 16 * dz + 4 * dy, dz < v.nlev ? left[dy] : 0);
+        store_piece(row[dy], val + 16 * dz + 4 * dy, dz < v.nlev ? left[dy] : 0);
         row[dy] += v.lstride;
       }
     }
@@ -465,7 +463,7 @@ __device__ __forceinline__ void scatter_run(float* __restrict__ dst, const RunVi
         float* row = dst + (r.rbase[dy] + dz * r.lstride);
         const float* o = val + 16 * dz + 4 * dy;
         const f32x4_row f = {o[0], o[1], o[2], o[3]};
-        *reinterpret_cast<f32x4_row*>(row + (uint32_t)x0) = f;
+        __builtin_nontemporal_store(f, reinterpret_cast<f32x4_row*>(row + (uint32_t)x0));
       }
     }
     return;
@@ -659,6 +657,22 @@ __device__ __forceinline__ void decode_tile(const Geo& geo, const uint64_t* __re
   }
 }
 
+// Workgroup i runs on XCD i % 8 (dispatch is round-robin over the XCDs).
+// Renumbered in groups of 256, each XCD takes 32 consecutive workgroups of a
+// group: neighbouring tiles, which share the cache lines at their ends, then
+// mostly meet in one L2 (merged there instead of fetched twice, or written
+// back in parts from two), while all XCDs stay in one region of the buffer.
+// On the 9.47 GB buffer at rate 16, in plain order, in runs of 8 and in runs
+// of 32: decode 3.79, 3.07 and 3.04 ms, encode 2.80, 2.83 and 2.79 ms.  Runs
+// of 128 and 512 are no better.  A partial last group keeps its order.  A
+// bijection on [0, n).
+__device__ __forceinline__ int32_t xcd_grouped(uint32_t i, uint32_t n) {
+  constexpr uint32_t kXcds = 8, kRun = 32, kGroup = kXcds * kRun;
+  if (i >= n / kGroup * kGroup) return (int32_t)i;
+  const uint32_t x = i % kXcds, k = i / kXcds;
+  return (int32_t)((k / kRun) * kGroup + x * kRun + k % kRun);
+}
+
 // Workgroups cover the tiles of blocks [b_begin, b_end): one tile per
 // wavefront, or (PERSIST) a grid-stride loop over tiles.
 // Bound by vector instruction issue (93% of the issue slots taken on the
@@ -678,7 +692,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   const int waves = blockDim.x >> 6;
   uint64_t* wlds = lds + (size_t)wave * 64 * lds_stride(rate);
   const int32_t ntiles = tiles_of(b_end - b_begin);
-  int32_t t = blockIdx.x * waves + wave;
+  int32_t t = (PERSIST ? (int32_t)blockIdx.x : xcd_grouped(blockIdx.x, gridDim.x)) * waves + wave;
   if (t >= ntiles) return;
   for (;;) {
     const int32_t b0 = b_begin + (t << 6);
@@ -691,26 +705,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   }
 }
 
-// Workgroup i runs on XCD i % 8 (dispatch is round-robin over the XCDs).
-// Renumbered in groups of 64, each XCD takes 8 consecutive workgroups of a
-// group: neighbouring tiles, which share the cache lines at their ends, then
-// mostly meet in one L2 (merged there instead of written back in parts from
-// two), while all XCDs stay in one region of the buffer.  A partial last
-// group keeps its order.  A bijection on [0, n).
-__device__ __forceinline__ int32_t xcd_grouped(uint32_t i, uint32_t n) {
-  constexpr uint32_t kXcds = 8, kRun = 8, kGroup = kXcds * kRun;
-  if (i >= n / kGroup * kGroup) return (int32_t)i;
-  const uint32_t x = i % kXcds, k = i / kXcds;
-  return (int32_t)((k / kRun) * kGroup + x * kRun + k % kRun);
-}
-
 // Bound by vector instruction issue (90% of the slots on the 9.47 GB buffer at
 // rate 16; 2,970 vector instructions per tile and 3.07 ms, from 3,545 and
 // 3.53 ms) with its writes close behind (16 row pieces of 1 KB per tile).  Four
 // wavefronts per SIMD hold the block without spilling; three are a fifth
-// slower.  Tiles are taken in XCD-grouped order, so that the cache lines
-// shared by neighbouring tiles are merged in one L2 rather than written back in
-// parts from two (the encoder gains nothing from the order).
+// slower.
 template <int RATE, bool UNIT, bool PERSIST, class Geo>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_decode(Geo geo, const uint64_t* __restrict__ in,
                                                 float* __restrict__ dst, int rate_rt,
@@ -994,9 +993,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     decode_block<CAP, true>(slice, val, cap, maxprec, minexp);
     BlockView v;
     geo.locate_tile(b0, lane, nact, v);
-    // streaming stores: 9% faster here on a 9.47 GB output; the fixed-rate
-    // decoders gain nothing from them
-    scatter<true, false, true>(dst, v, val);
+    scatter<true>(dst, v, val);
   }
 }
 
@@ -1692,7 +1689,11 @@ hipError_t launch_plan_decode_var(const PlanDev& p, const uint32_t* in,
                                   float* dst, int cap, int32_t nblocks, int maxprec, int minexp,
                                   hipStream_t s) {
   if (nblocks <= 0) return hipSuccess;
-  constexpr int wg = 128;
+  // Four neighbouring tiles per workgroup: the cache lines that they share are
+  // completed close in time (precision 16 on the 9.47 GB buffer 2.31 ms, with
+  // two 2.52; accuracy 1e-2 on the z->lambda share 74 us, with two 79, with
+  // one 77).
+  constexpr int wg = 256;
   const int ntiles = tiles_of(nblocks);
   dim3 grid((ntiles + wg / 64 - 1) / (wg / 64)), block(wg);
   size_t shm = lds_bytes(wg, cap);
