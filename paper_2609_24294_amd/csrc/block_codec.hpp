@@ -411,6 +411,15 @@ ZFPX_HD void pin_words(Words3& a) {
 #endif
 }
 
+// x as 64 bits, x not known to the compiler (which would keep a constant upper
+// half in a register of its own throughout a loop around the coder).
+ZFPX_HD uint64_t sign_extended(int32_t x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm("" : "+v"(x));
+#endif
+  return (uint64_t)(int64_t)x;
+}
+
 // A value that is the same in every active lane, in a scalar register.
 ZFPX_HD int uniform_int(int x) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -609,7 +618,7 @@ ZFPX_HD uint32_t encode_block(float* v, uint64_t* out, int rate_rt, int maxprec 
           if (hs <= 62) {
             // -2^(hs+2) for the group test that does not follow the last one,
             // and -2^(hs+1) for its own one if implied
-            const uint64_t cut = (~(uint64_t)0 - 1 - last) << (hs + 1);
+            const uint64_t cut = sign_extended(last ? -3 : -2) << (hs + 1);
             const uint64_t sp = spread_ranks(y);
             or_bits(out, gpos, shift_add64<2>(sp, shift_add64<1>(sp, cut + 1)));
             pos = gpos + hs + 3 - 2 * last;  // and the closing group test 0
