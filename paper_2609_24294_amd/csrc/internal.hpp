@@ -33,7 +33,7 @@ __host__ __device__ inline int32_t tiles_of(int32_t n) {
 // Launch configuration: threads per workgroup and persistent grid (0 = one
 // 64-block tile per wavefront).
 struct LaunchCfg {
-  int wg = 128;
+  int wg = 64;
   int grid = 0;
 };
 

@@ -1697,7 +1697,7 @@ hipError_t launch_plan_encode_var(const PlanDev& p, const float* src, uint32_t* 
                                   uint32_t* stage, uint32_t* tile_count, int cap,
                                   int32_t nblocks, int maxprec, int minexp, hipStream_t s) {
   if (nblocks <= 0) return hipSuccess;
-  constexpr int wg = 128;
+  constexpr int wg = 64;  // as for fixed rate (with 128 the share takes 1% longer)
   const int ntiles = tiles_of(nblocks);
   dim3 grid((ntiles + wg / 64 - 1) / (wg / 64)), block(wg);
   size_t shm = lds_bytes(wg, cap);
