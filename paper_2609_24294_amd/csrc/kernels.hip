@@ -486,9 +486,11 @@ __device__ __forceinline__ void pin_words32(uint32_t (&v)[8]) {
 }
 
 // Copy a tile's coded words between LDS slices (stride words per block) and
-// global memory (rate words per block, contiguous).  For rates dividing 64,
-// lane l always handles word l % rate of every (64/rate)-th block, so the
-// addresses are a per-lane base plus compile-time offsets.
+// global memory (rate words per block, contiguous).  For rates dividing 64, a
+// lane's words lie at the same place of every n-th block, so the addresses are
+// a per-lane base plus compile-time offsets; whole tiles move two words per
+// lane and access (against one: small field 24.7 -> 24.3 us, z->lambda share
+// 75.0 -> 74.0 us encoding and 86.3 -> 85.4 decoding at rate 16).
 template <bool COH>
 __device__ __forceinline__ void gstore64(uint64_t* p, uint64_t v) {
   if (COH)
@@ -502,6 +504,9 @@ __device__ __forceinline__ uint64_t gload64(const uint64_t* p) {
   return *p;
 }
 
+// Two stream words; the stream is aligned to one.
+typedef uint64_t u64x2_words __attribute__((ext_vector_type(2), aligned(8)));
+
 template <int RATE, bool TO_GLOBAL, bool COH = false>
 __device__ __forceinline__ void copy_tile(uint64_t* __restrict__ g, uint64_t* lds, int lane,
                                           int nact, int rate_rt) {
@@ -510,6 +515,35 @@ __device__ __forceinline__ void copy_tile(uint64_t* __restrict__ g, uint64_t* ld
     constexpr int step = 64 / RATE;  // blocks per row of 64 words
     const int b = lane / RATE, idx = lane % RATE;
     uint64_t* l = lds + b * stride + idx;
+    if (nact == 64 && !COH) {
+      // A whole tile (nact is wave-uniform), two words per lane and access (a
+      // block's words are an even number): every read is issued before any is
+      // waited for, one round trip in all (behind per-word guards the compiler
+      // waits for each word before the next).
+      constexpr int pairs = RATE / 2, pair_step = 64 / pairs;
+      uint64_t* l2 = lds + lane / pairs * stride + 2 * (lane % pairs);
+      u64x2_words* g2 = reinterpret_cast<u64x2_words*>(g) + lane;
+      u64x2_words v[pairs];
+      if (TO_GLOBAL) {
+#pragma unroll
+        for (int j = 0; j < pairs; j++) {
+          const uint64_t* w = l2 + j * pair_step * stride;
+          v[j] = u64x2_words{w[0], w[1]};
+        }
+#pragma unroll
+        for (int j = 0; j < pairs; j++) __builtin_nontemporal_store(v[j], g2 + 64 * j);
+      } else {
+#pragma unroll
+        for (int j = 0; j < pairs; j++) v[j] = g2[64 * j];
+#pragma unroll
+        for (int j = 0; j < pairs; j++) {
+          uint64_t* w = l2 + j * pair_step * stride;
+          w[0] = v[j].x;
+          w[1] = v[j].y;
+        }
+      }
+      return;
+    }
     if (nact == 64) {
       // A whole tile (nact is wave-uniform): every read is issued before any
       // is waited for, one round trip in all (behind per-word guards the

@@ -84,3 +84,16 @@ def test_row_widths_around_a_tile(zfpx_lib, nx, nz, ny):
         out = torch.full_like(d, float("nan"))
         zfpx_lib.zfpx_decode_fixed_rate(words, rate, out)
         assert np.array_equal(_bits(out.cpu()), _bits(oracle.decode_regular(want, a.shape, rate)))
+
+
+@pytest.mark.parametrize("rate", [8, 16, 32])
+def test_streams_off_a_16_byte_boundary(zfpx_lib, rate):
+    rng = np.random.default_rng(rate)
+    a = np.cumsum(rng.standard_normal((4, 8, 1200)), 2).astype(np.float32)
+    want = oracle.encode_regular(a, rate)
+    room = torch.zeros(want.size + 1, dtype=torch.int64, device=DEV)
+    zfpx_lib.zfpx_encode_fixed_rate(torch.from_numpy(a).to(DEV), rate, room[1:])
+    assert np.array_equal(_u64(room[1:]), want)
+    out = torch.full(a.shape, float("nan"), device=DEV)
+    zfpx_lib.zfpx_decode_fixed_rate(room[1:], rate, out)
+    assert np.array_equal(_bits(out.cpu()), _bits(oracle.decode_regular(want, a.shape, rate)))
