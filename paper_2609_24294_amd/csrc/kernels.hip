@@ -6,8 +6,8 @@
 // segments a lane reads are contiguous 16-byte pieces and a wavefront's loads
 // of one row are one contiguous 1 KiB stretch).  The coded words of a tile are
 // contiguous in the output, so each lane codes into its own slice of LDS
-// (stride rate|1 words to spread the banks) and the wavefront then copies the
-// tile out (or in, for decoding) with coalesced 8-byte accesses.  Workgroups
+// (an odd stride to spread the banks) and the wavefront then copies the tile
+// out (or in, for decoding) with coalesced 16-byte accesses.  Workgroups
 // loop over tiles with a grid stride, so the same kernel serves as a
 // one-tile-per-wave launch and as a persistent launch.
 #include <hip/hip_runtime.h>
@@ -710,11 +710,11 @@ __device__ __forceinline__ int32_t xcd_grouped(uint32_t i, uint32_t n) {
 // Workgroups cover the tiles of blocks [b_begin, b_end): one tile per
 // wavefront, or (PERSIST) a grid-stride loop over tiles.
 // Bound by vector instruction issue (93% of the issue slots taken on the
-// 9.47 GB buffer at rate 16; 2,909 vector instructions per tile and 2.80 ms,
-// from 3,407 and 3.21 ms with a loop over groups wherever coefficient 63 was
-// reached).  Four wavefronts per SIMD (at rate 16 as many as the LDS slices
-// allow) let instructions of two of them issue together more often than
-// three; five, possible at rate 8, are no faster.
+// 9.47 GB buffer at rate 16; 2,916 vector instructions per tile, where a loop
+// over groups wherever coefficient 63 is reached took 3,407: 2.69 to 2.82 ms on
+// three cards with the XCD-grouped order, from 3.21 to 3.27).  Four wavefronts per SIMD (at rate 16 as many
+// as the LDS slices allow) let instructions of two of them issue together more
+// often than three; five, possible at rate 8, spill and are 5 to 25% slower.
 template <int RATE, bool UNIT, bool PERSIST, class Geo>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_encode(Geo geo, const float* __restrict__ src,
                                                 uint64_t* __restrict__ out, int rate_rt,
@@ -739,9 +739,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   }
 }
 
-// Bound by vector instruction issue (90% of the slots on the 9.47 GB buffer at
-// rate 16; 2,970 vector instructions per tile and 3.07 ms, from 3,545 and
-// 3.53 ms) with its writes close behind (16 row pieces of 1 KB per tile).  Four
+// Bound by vector instruction issue (87% of the slots on the 9.47 GB buffer at
+// rate 16; 2,825 vector instructions per tile and 2.93 to 3.06 ms on three
+// cards, from 3,380 and 3.51) with its writes close behind (16 row pieces of 1 KB per tile).  Four
 // wavefronts per SIMD hold the block without spilling; three are a fifth
 // slower.
 template <int RATE, bool UNIT, bool PERSIST, class Geo>
