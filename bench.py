@@ -37,7 +37,8 @@ VALU_SIMD_CYCLES_PER_S = 1024 * 2.4e9  # 256 CUs x 4 SIMDs at 2.4 GHz
 
 KERNEL_SOURCES = ("paper_2609_24294_amd/csrc/kernels.hip",
                   "paper_2609_24294_amd/csrc/block_codec.hpp",
-                  "paper_2609_24294_amd/csrc/internal.hpp")
+                  "paper_2609_24294_amd/csrc/internal.hpp",
+                  "paper_2609_24294_amd/csrc/regular_geo.hpp")
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "o2560_l90_hbm_traffic.md")
 
 LEGS = ("share", "small", "accuracy", "variable", "sensitivity", "pipeline", "fourier",

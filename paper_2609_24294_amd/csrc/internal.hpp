@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "plan_tables.hpp"
+#include "regular_geo.hpp"
 
 namespace zfpx {
 
@@ -15,13 +16,6 @@ struct PlanDev {
   const SegDesc* segs;
   const int32_t* seg_block0;  // [nseg + 9], the last 9 entries = total blocks
   const int32_t* tile_seg;    // [ntiles]: run holding block 64 * t
-};
-
-// Regular strided array as a geometry.
-struct RegularDev {
-  int64_t nx, ny, nz;
-  int64_t sx, sy, sz;
-  int32_t nbx, nby;
 };
 
 // 64-block tiles covering n blocks (n up to 2^31 - 1, counted without

@@ -32,32 +32,12 @@ typedef float f32x2_row __attribute__((ext_vector_type(2), aligned(4)));
 // Block location
 // ---------------------------------------------------------------------------
 
-struct BlockView {
-  int64_t rbase[4];
-  int64_t lstride;
-  int64_t sx;
-  int32_t nlev, nrow;
-  int32_t rlen[4];
-  int32_t x0;  // first x of the block
-};
-
 // Loads through the constant address space: with a wave-uniform address they
 // become scalar loads (no per-lane round trip).
 template <class T>
 __device__ __forceinline__ T uniform_load(const T* p, int64_t i) {
   return ((const __attribute__((address_space(4))) T*)p)[i];
 }
-
-// A tile whose 64 blocks all lie in one run: everything but the x offset is
-// wave-uniform (scalar registers), so whole blocks load through a scalar row
-// base plus a per-lane offset.
-struct RunView {
-  int64_t rbase[4];
-  int64_t lstride;
-  int32_t nlev, nrow, block0;
-  int32_t minlen;  // shortest row of the group
-  int32_t rlen[4];
-};
 
 struct PlanGeo {
   PlanDev p;
@@ -143,63 +123,6 @@ struct PlanGeo {
     v.nlev = second ? nl1 : nl0;
     v.nrow = second ? nr1 : nr0;
     v.x0 = 4 * (b - (second ? bb1 : bb0));
-  }
-};
-
-struct RegularGeo {
-  RegularDev g;
-  // u / d for u < d + 64: at most one row further where d >= 64; below, an
-  // exact multiply (u < 128).
-  static __device__ __forceinline__ uint32_t wraps(uint32_t u, uint32_t d) {
-    if (d >= 64) return u >= d ? 1u : 0u;
-    return (u * ((65536u + d - 1) / d)) >> 16;
-  }
-  // Block b0 + lane: the divisions are those of the wave-uniform b0.
-  __device__ __forceinline__ void locate_tile(int32_t b0, int lane, int, BlockView& v) const {
-    const uint32_t t0 = (uint32_t)b0 / (uint32_t)g.nbx;
-    uint32_t bx = (uint32_t)b0 - t0 * (uint32_t)g.nbx + (uint32_t)lane;
-    uint32_t bz = t0 / (uint32_t)g.nby;
-    uint32_t by = t0 - bz * (uint32_t)g.nby;
-    const uint32_t rows = wraps(bx, (uint32_t)g.nbx);
-    bx -= rows * (uint32_t)g.nbx;
-    by += rows;
-    const uint32_t planes = wraps(by, (uint32_t)g.nby);
-    by -= planes * (uint32_t)g.nby;
-    bz += planes;
-    const int64_t y0 = 4 * (int64_t)by, z0 = 4 * (int64_t)bz;
-    const int64_t zoff = z0 * g.sz;
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      int64_t y = y0 + i < g.ny ? y0 + i : g.ny - 1;
-      v.rbase[i] = zoff + y * g.sy;
-      v.rlen[i] = (int32_t)g.nx;
-    }
-    v.lstride = g.sz;
-    v.sx = g.sx;
-    v.nlev = (int32_t)(g.nz - z0 < 4 ? g.nz - z0 : 4);
-    v.nrow = (int32_t)(g.ny - y0 < 4 ? g.ny - y0 : 4);
-    v.x0 = (int32_t)(4 * bx);
-  }
-  // A tile within one row of blocks (every tile but those at row ends): the
-  // same view as a plan's run.  Rows of fewer blocks than a tile have none.
-  __device__ __forceinline__ bool one_run(int32_t b0, int nact, RunView& r) const {
-    if (nact > g.nbx) return false;
-    const uint32_t t = (uint32_t)b0 / (uint32_t)g.nbx;
-    const uint32_t bx0 = (uint32_t)b0 - t * (uint32_t)g.nbx;
-    if (bx0 + (uint32_t)nact > (uint32_t)g.nbx) return false;
-    const uint32_t bz = t / (uint32_t)g.nby;
-    const int64_t y0 = 4 * (int64_t)(t - bz * (uint32_t)g.nby), z0 = 4 * (int64_t)bz;
-#pragma unroll
-    for (int i = 0; i < 4; i++) {
-      r.rbase[i] = z0 * g.sz + (y0 + i < g.ny ? y0 + i : g.ny - 1) * g.sy;
-      r.rlen[i] = (int32_t)g.nx;
-    }
-    r.lstride = g.sz;
-    r.nlev = (int32_t)(g.nz - z0 < 4 ? g.nz - z0 : 4);
-    r.nrow = (int32_t)(g.ny - y0 < 4 ? g.ny - y0 : 4);
-    r.block0 = b0 - (int32_t)bx0;
-    r.minlen = (int32_t)g.nx;
-    return true;
   }
 };
 
