@@ -73,7 +73,8 @@ int zfpx_device_cus(void);
  * Coded size in bytes of an nx*ny*nz array at `rate` bits per value:
  * ceil(nx/4)*ceil(ny/4)*ceil(nz/4) * 8 * rate (fixed-rate mode gives every
  * block exactly 64*rate bits; paper Section II-C and Table 1).  Returns a
- * negative zfpx_status for a bad rate or negative sizes.
+ * negative zfpx_status for a bad rate, negative sizes or a size that does not
+ * fit 64 bits.
  */
 int64_t zfpx_fixed_rate_bytes(int64_t nx, int64_t ny, int64_t nz, int rate);
 
@@ -84,7 +85,8 @@ int64_t zfpx_fixed_rate_bytes(int64_t nx, int64_t ny, int64_t nz, int rate);
  * `rate` bits per value).
  *   d_out     : device, 8-byte aligned, at least zfpx_fixed_rate_bytes(...)
  *               bytes (out_bytes); ZFPX_ENOSPC if smaller.
- *   nx,ny,nz  : >= 0; an empty array enqueues nothing.
+ *   nx,ny,nz  : >= 0, at most 2^31-1 blocks in all (EINVAL); an empty array
+ *               enqueues nothing.
  * The caller guarantees that every element offset is inside d_in.
  */
 int zfpx_encode_fixed_rate(const float* d_in, int64_t nx, int64_t ny, int64_t nz, int64_t sx,

@@ -89,8 +89,10 @@ int zfpx_device_cus(void) { return device_cu_count(); }
 
 int64_t zfpx_fixed_rate_bytes(int64_t nx, int64_t ny, int64_t nz, int rate) {
   if (!rate_ok(rate) || nx < 0 || ny < 0 || nz < 0) return ZFPX_EINVAL;
-  int64_t nb = ceil4(nx) * ceil4(ny) * ceil4(nz);
-  return nb * 8 * rate;
+  const int64_t nb = regular_blocks(nx, ny, nz);
+  int64_t bytes;
+  if (nb < 0 || __builtin_mul_overflow(nb, (int64_t)(8 * rate), &bytes)) return ZFPX_EINVAL;
+  return bytes;
 }
 
 // ---------------------------------------------------------------------------
@@ -100,11 +102,11 @@ int64_t zfpx_fixed_rate_bytes(int64_t nx, int64_t ny, int64_t nz, int rate) {
 static int regular_setup(int64_t nx, int64_t ny, int64_t nz, int64_t sx, int64_t sy, int64_t sz,
                          int rate, RegularDev* g, int64_t* nblocks) {
   if (!rate_ok(rate) || nx < 0 || ny < 0 || nz < 0) return ZFPX_EINVAL;
-  int64_t nbx = ceil4(nx), nby = ceil4(ny), nbz = ceil4(nz);
-  int64_t nb = nbx * nby * nbz;
-  if (nb > kMaxBlocks) return ZFPX_EINVAL;
-  *g = RegularDev{nx, ny, nz, sx, sy, sz, (int32_t)nbx, (int32_t)nby};
+  const int64_t nb = regular_blocks(nx, ny, nz);
+  if (nb < 0 || nb > kMaxBlocks) return ZFPX_EINVAL;
   *nblocks = nb;
+  if (nb == 0) return ZFPX_OK;
+  *g = RegularDev{nx, ny, nz, sx, sy, sz, (int32_t)ceil4(nx), (int32_t)ceil4(ny)};
   return ZFPX_OK;
 }
 

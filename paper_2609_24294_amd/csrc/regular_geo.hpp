@@ -44,6 +44,16 @@ struct RegularDev {
   int32_t nbx, nby;
 };
 
+// 4x4x4 blocks of an nx x ny x nz array (sizes >= 0), or -1 if their number
+// passes 64 bits.
+inline int64_t regular_blocks(int64_t nx, int64_t ny, int64_t nz) {
+  if (nx == 0 || ny == 0 || nz == 0) return 0;
+  const int64_t bx = (nx - 1) / 4 + 1, by = (ny - 1) / 4 + 1, bz = (nz - 1) / 4 + 1;
+  int64_t n;
+  if (__builtin_mul_overflow(bx, by, &n) || __builtin_mul_overflow(n, bz, &n)) return -1;
+  return n;
+}
+
 struct RegularGeo {
   RegularDev g;
   // Positions within a row are 32-bit, a row may be longer (nx up to four

@@ -62,8 +62,8 @@ struct Result {
 bool request_ok(const zfpx_request* rq, int64_t* nblocks, size_t* bytes) {
   if (!rq || (rq->op != 0 && rq->op != 1) || rq->rate < 1 || rq->rate > 32) return false;
   if (rq->nx < 1 || rq->ny < 1 || rq->nz < 1 || !rq->d_in || !rq->d_out) return false;
-  int64_t nb = ceil4(rq->nx) * ceil4(rq->ny) * ceil4(rq->nz);
-  if (nb > 0x7fffffffLL) return false;
+  const int64_t nb = regular_blocks(rq->nx, rq->ny, rq->nz);
+  if (nb < 0 || nb > kMaxPlanBlocks) return false;
   const void* words = rq->op == 0 ? rq->d_out : rq->d_in;
   if (((uintptr_t)words & 7) != 0) return false;
   *nblocks = nb;

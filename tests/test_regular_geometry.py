@@ -66,3 +66,25 @@ def test_blocks_of_regular_arrays(dump_exe, dims, form):
     assert seen == sum(min(64, nb - 64 * t) for t in picks)
     if form == "unit" and nbx >= 1024:
         assert runs > 0
+
+
+@pytest.mark.parametrize("dims", [(1 << 24, 1 << 24, 1 << 24), (1 << 23, 1 << 23, 1 << 23),
+                                  (B32, B31, 4), ((1 << 63) - 1, 2, 2), (4 * B31, 1, 1)])
+def test_more_blocks_than_an_array_may_have(dims):
+    """Counts past 2^31 - 1, also where the product of the three passes 64
+    bits, are refused: nothing is launched on a count that wrapped."""
+    from paper_2609_24294_amd import zfpx
+    nx, ny, nz = dims
+    blocks = -(-nx // 4) * -(-ny // 4) * -(-nz // 4)
+    L, fake = zfpx.library(), 4096  # never dereferenced
+    if blocks * 8 * 16 >= 1 << 63:
+        assert L.zfpx_fixed_rate_bytes(nx, ny, nz, 16) == zfpx.EINVAL
+    else:
+        assert L.zfpx_fixed_rate_bytes(nx, ny, nz, 16) == blocks * 8 * 16
+    assert L.zfpx_encode_fixed_rate(fake, nx, ny, nz, 1, 0, 0, 16, fake, (1 << 64) - 1,
+                                    None) == zfpx.EINVAL
+    assert L.zfpx_decode_fixed_rate(fake, (1 << 64) - 1, nx, ny, nz, 1, 0, 0, 16, fake,
+                                    None) == zfpx.EINVAL
+    # no elements, whatever the other sizes: nothing to do
+    assert L.zfpx_encode_fixed_rate(None, nx, 0, nz, 1, 0, 0, 16, None, 0, None) == zfpx.OK
+    assert L.zfpx_fixed_rate_bytes(nx, ny, 0, 16) == 0
