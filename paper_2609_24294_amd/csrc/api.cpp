@@ -45,6 +45,7 @@ bool cfg_ok(LaunchCfg c, int rate) {
 struct zfpx_plan {
   int32_t nchunks = 0;
   int64_t nblocks = 0, nvalues = 0, min_elems = 0;
+  bool vec4 = true;
   std::vector<int64_t> chunk_blocks, chunk_first;  // host copies
   std::vector<int64_t> shape_key;                   // for the tuning cache
   SegDesc* d_segs = nullptr;
@@ -173,6 +174,7 @@ int zfpx_plan_create(int32_t nchunks, const int64_t* chunk_base, const int64_t* 
   p->nblocks = t.nblocks;
   p->nvalues = t.nvalues;
   p->min_elems = t.min_elems;
+  p->vec4 = t.vec4;
   p->shape_key = {nchunks, t.nblocks, t.nvalues, (int64_t)t.segs.size()};
   const std::vector<SegDesc>& segs = t.segs;
   if (!segs.empty()) {
@@ -483,7 +485,7 @@ int zfpx_plan_decode_var(const zfpx_plan* p, const uint32_t* d_words, size_t wor
     return ZFPX_EINVAL;
   hipError_t e = launch_plan_decode_var(p->dev, d_words, words_bytes / 4, d_nd, d_tile_off,
                                         d_dst, rate_cap, (int32_t)p->nblocks, maxprec, minexp,
-                                        (hipStream_t)stream);
+                                        p->vec4 && aligned(d_dst, 16), (hipStream_t)stream);
   return e == hipSuccess ? ZFPX_OK : ZFPX_EHIP;
 }
 

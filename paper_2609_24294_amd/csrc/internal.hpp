@@ -55,10 +55,11 @@ hipError_t launch_plan_encode_var(const PlanDev& p, const float* src, uint32_t* 
                                   uint64_t out_words, uint8_t* nd, int64_t* tile_off,
                                   uint32_t* stage, uint32_t* tile_count, int cap,
                                   int32_t nblocks, int maxprec, int minexp, hipStream_t s);
+// stream: whole tiles are stored with the non-temporal hint.
 hipError_t launch_plan_decode_var(const PlanDev& p, const uint32_t* in,
                                   uint64_t in_words, const uint8_t* nd, const int64_t* tile_off,
                                   float* dst, int cap, int32_t nblocks, int maxprec, int minexp,
-                                  hipStream_t s);
+                                  bool stream, hipStream_t s);
 // Scratch of the allocation-free variable-size encoder: a file-scope device
 // array of kNoAllocScratchBytes (kernels.hip), one copy per GPU.  Returns its
 // address on the current device (looked up once per device).

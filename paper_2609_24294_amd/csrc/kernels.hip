@@ -14,6 +14,7 @@
 
 #include <cstddef>
 #include <mutex>
+#include <type_traits>
 
 #include "block_codec.hpp"
 #include "internal.hpp"
@@ -246,14 +247,15 @@ __device__ __forceinline__ void gather(const float* __restrict__ src, const Bloc
 }
 
 // A row's piece: 16 bytes, or the row's last one to three points in pieces of
-// eight and four bytes.  The 16-byte stores are streaming (non-temporal): every
-// byte is written once.  Rows of short runs gain most (decoding the
-// Fourier-space share at rate 12, 320-byte pieces: 38.0 against 48.0 us), other
-// shapes 0 to 4%.
+// eight and four bytes.  STREAM: a non-temporal store.
+template <bool STREAM = false>
 __device__ __forceinline__ void store_piece(float* q, const float* o, int left) {
   if (left >= 4) {
     const f32x4_row f = {o[0], o[1], o[2], o[3]};
-    __builtin_nontemporal_store(f, reinterpret_cast<f32x4_row*>(q));
+    if (STREAM)
+      __builtin_nontemporal_store(f, reinterpret_cast<f32x4_row*>(q));
+    else
+      *reinterpret_cast<f32x4_row*>(q) = f;
   } else if (left > 0) {
     const float a = o[0], c = o[2];
     if (left >= 2) *reinterpret_cast<f32x2_row*>(q) = f32x2_row{a, o[1]};
@@ -261,7 +263,21 @@ __device__ __forceinline__ void store_piece(float* q, const float* o, int left) 
   }
 }
 
-template <bool UNIT, bool COH = false>
+// Decoded values are what the caller reads next, so the fixed-rate decoders
+// store them with ordinary stores, which leave them in the caches.  Streaming
+// (non-temporal) stores end the decoder sooner where rows are short (the
+// Fourier-space share at rate 12: 37 against 46 us) and later where long rows
+// lie off the cache lines at low rates (the z->lambda share at rate 4: 78
+// against 63 us; the 9.47 GB buffer: 2.65 against 2.13 ms), and the reader pays
+// for them either way: decoding and then taking the maximum of the result is 76
+// against 70 us on that Fourier-space share, 146 against 126 on the z->lambda
+// share at rate 8, 31 against 25 on a 256 KiB field at rate 16.
+// STREAM (the variable-size decoder, plans whose rows are all 16-byte
+// aligned): tiles of whole blocks are stored with streaming stores; at precision
+// 16 on the Fourier-space share 41 against 49 us, on a share of 640-point rows
+// 30 against 36, and with a copy of the result behind it 74 against 78 and 62
+// against 63.
+template <bool UNIT, bool COH = false, bool STREAM = false>
 __device__ __forceinline__ void scatter(float* __restrict__ dst, const BlockView& v,
                                         const float* val, uint32_t vspan = 0) {
   if (COH && vspan != 0 && whole_block(v)) {
@@ -293,7 +309,7 @@ __device__ __forceinline__ void scatter(float* __restrict__ dst, const BlockView
       for (int dz = 0; dz < 4; dz++) {
 #pragma unroll
         for (int dy = 0; dy < 4; dy++) {
-          store_piece(row[dy], val + 16 * dz + 4 * dy, 4);
+          store_piece<STREAM>(row[dy], val + 16 * dz + 4 * dy, 4);
           row[dy] += v.lstride;
         }
       }
@@ -386,7 +402,7 @@ __device__ __forceinline__ void scatter_run(float* __restrict__ dst, const RunVi
         float* row = dst + (r.rbase[dy] + dz * r.lstride);
         const float* o = val + 16 * dz + 4 * dy;
         const f32x4_row f = {o[0], o[1], o[2], o[3]};
-        __builtin_nontemporal_store(f, reinterpret_cast<f32x4_row*>(row + (uint32_t)x0));
+        *reinterpret_cast<f32x4_row*>(row + (uint32_t)x0) = f;
       }
     }
     return;
@@ -941,7 +957,8 @@ __global__ __launch_bounds__(256) void k_var_place(const uint32_t* __restrict__ 
 
 // Any content of the stream, counts and offsets decodes without a fault:
 // counts are clamped to the cap and words outside the stream read as zero.
-template <int CAP, class Geo>
+// STREAM: every row of the plan is 16-byte aligned.
+template <int CAP, bool STREAM, class Geo>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_decode_var(
     Geo geo, const uint32_t* __restrict__ in, uint64_t in_words, const uint8_t* __restrict__ nd_in,
     const int64_t* __restrict__ tile_off, float* __restrict__ dst, int cap_rt, int32_t nblocks,
@@ -987,7 +1004,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
     decode_block<CAP, true>(slice, val, cap, maxprec, minexp);
     BlockView v;
     geo.locate_tile(b0, lane, nact, v);
-    scatter<true>(dst, v, val);
+    scatter<true, false, STREAM>(dst, v, val);
   }
 }
 
@@ -1622,21 +1639,16 @@ hipError_t launch_f16_restore(const uint16_t* in, size_t n, float* out, hipStrea
   return hipGetLastError();
 }
 
-#define ZFPX_CAP_SWITCH(KERNEL, GEO, ...)                                     \
-  switch (cap) {                                                                   \
-    case 8:                                                                        \
-      hipLaunchKernelGGL((KERNEL<8, GEO>), grid, block, shm, s, __VA_ARGS__);  \
-      break;                                                                       \
-    case 16:                                                                       \
-      hipLaunchKernelGGL((KERNEL<16, GEO>), grid, block, shm, s, __VA_ARGS__); \
-      break;                                                                       \
-    case 32:                                                                       \
-      hipLaunchKernelGGL((KERNEL<32, GEO>), grid, block, shm, s, __VA_ARGS__); \
-      break;                                                                       \
-    default:                                                                       \
-      hipLaunchKernelGGL((KERNEL<0, GEO>), grid, block, shm, s, __VA_ARGS__);  \
-      break;                                                                       \
+// Calls launch with the cap as a constant (0: a cap without a kernel of its own).
+template <class F>
+static void with_cap(int cap, F launch) {
+  switch (cap) {
+    case 8: return launch(std::integral_constant<int, 8>());
+    case 16: return launch(std::integral_constant<int, 16>());
+    case 32: return launch(std::integral_constant<int, 32>());
+    default: return launch(std::integral_constant<int, 0>());
   }
+}
 
 size_t var_stage_words(int64_t nblocks, int cap) {
   return (size_t)((nblocks + 63) >> 6) * 64 * 2 * (size_t)cap;
@@ -1659,8 +1671,10 @@ hipError_t launch_plan_encode_var(const PlanDev& p, const float* src, uint32_t* 
   dim3 grid((ntiles + wg / 64 - 1) / (wg / 64)), block(wg);
   size_t shm = lds_bytes(wg, cap);
   PlanGeo geo{p};
-  ZFPX_CAP_SWITCH(k_encode_var, PlanGeo, geo, src, stage, tile_count, nd, cap, nblocks,
-                    maxprec, minexp);
+  with_cap(cap, [&](auto c) {
+    hipLaunchKernelGGL((k_encode_var<decltype(c)::value, PlanGeo>), grid, block, shm, s, geo, src,
+                       stage, tile_count, nd, cap, nblocks, maxprec, minexp);
+  });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const int32_t nchunks = (int32_t)(((int64_t)ntiles + kScanChunk - 1) / kScanChunk);
@@ -1684,7 +1698,7 @@ hipError_t launch_plan_encode_var(const PlanDev& p, const float* src, uint32_t* 
 hipError_t launch_plan_decode_var(const PlanDev& p, const uint32_t* in,
                                   uint64_t in_words, const uint8_t* nd, const int64_t* tile_off,
                                   float* dst, int cap, int32_t nblocks, int maxprec, int minexp,
-                                  hipStream_t s) {
+                                  bool stream, hipStream_t s) {
   if (nblocks <= 0) return hipSuccess;
   // Four neighbouring tiles per workgroup: the cache lines that they share are
   // completed close in time (precision 16 on the 9.47 GB buffer 2.31 ms, with
@@ -1695,8 +1709,15 @@ hipError_t launch_plan_decode_var(const PlanDev& p, const uint32_t* in,
   dim3 grid((ntiles + wg / 64 - 1) / (wg / 64)), block(wg);
   size_t shm = lds_bytes(wg, cap);
   PlanGeo geo{p};
-  ZFPX_CAP_SWITCH(k_decode_var, PlanGeo, geo, in, in_words, nd, tile_off, dst, cap,
-                    nblocks, maxprec, minexp);
+  with_cap(cap, [&](auto c) {
+    constexpr int kCap = decltype(c)::value;
+    if (stream)
+      hipLaunchKernelGGL((k_decode_var<kCap, true, PlanGeo>), grid, block, shm, s, geo, in,
+                         in_words, nd, tile_off, dst, cap, nblocks, maxprec, minexp);
+    else
+      hipLaunchKernelGGL((k_decode_var<kCap, false, PlanGeo>), grid, block, shm, s, geo, in,
+                         in_words, nd, tile_off, dst, cap, nblocks, maxprec, minexp);
+  });
   return hipGetLastError();
 }
 
