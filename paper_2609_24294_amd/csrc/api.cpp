@@ -34,6 +34,18 @@ bool aligned(const void* p, uintptr_t a) { return ((uintptr_t)p & (a - 1)) == 0;
 // rate 8 (4%) and lose as much elsewhere.
 LaunchCfg default_cfg() { return LaunchCfg{}; }
 
+// Arrays with an x stride other than 1: two wavefronts once the launch has more
+// tiles than the card holds wavefronts (4,096), where neighbouring tiles share
+// the lines of all their rows and are best worked on together (64 x 512 x 1024
+// at rate 8: decoding with z closest in memory takes 356 us, with one wavefront
+// 396; encoding with y closest 117 against 139); below, one (8 x 64 x 128 with
+// z closest: encode 11.1 us, with two 13.0).
+LaunchCfg strided_cfg(bool unit, int64_t nblocks) {
+  LaunchCfg c = default_cfg();
+  if (!unit && nblocks > 64 * 4096) c.wg = 128;
+  return c;
+}
+
 bool cfg_ok(LaunchCfg c, int rate) {
   if (c.wg != 64 && c.wg != 128 && c.wg != 256) return false;
   if (c.grid < 0) return false;
@@ -122,7 +134,7 @@ int zfpx_encode_fixed_rate(const float* d_in, int64_t nx, int64_t ny, int64_t nz
   if (!d_in || !d_out || !aligned(d_out, 8)) return ZFPX_EINVAL;
   if ((int64_t)out_bytes < nb * 8 * rate) return ZFPX_ENOSPC;
   hipError_t e = launch_regular_encode(g, sx == 1, d_in, (uint64_t*)d_out,
-                                       rate, (int32_t)nb, default_cfg(),
+                                       rate, (int32_t)nb, strided_cfg(sx == 1, nb),
                                        (hipStream_t)stream);
   return e == hipSuccess ? ZFPX_OK : ZFPX_EHIP;
 }
@@ -138,7 +150,7 @@ int zfpx_decode_fixed_rate(const void* d_in, size_t in_bytes, int64_t nx, int64_
   if (!d_in || !d_out || !aligned(d_in, 8)) return ZFPX_EINVAL;
   if ((int64_t)in_bytes < nb * 8 * rate) return ZFPX_ENOSPC;
   hipError_t e = launch_regular_decode(g, sx == 1, (const uint64_t*)d_in,
-                                       d_out, rate, (int32_t)nb, default_cfg(),
+                                       d_out, rate, (int32_t)nb, strided_cfg(sx == 1, nb),
                                        (hipStream_t)stream);
   return e == hipSuccess ? ZFPX_OK : ZFPX_EHIP;
 }

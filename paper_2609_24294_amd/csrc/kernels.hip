@@ -631,19 +631,38 @@ __device__ __forceinline__ void decode_tile(const Geo& geo, const uint64_t* __re
 }
 
 // Workgroup i runs on XCD i % 8 (dispatch is round-robin over the XCDs).
-// Renumbered in groups of 256, each XCD takes 32 consecutive workgroups of a
-// group: neighbouring tiles, which share the cache lines at their ends, then
+// Renumbered in groups of 8 * 2^k, each XCD takes 2^k consecutive workgroups of
+// a group: neighbouring tiles, which share the cache lines at their ends, then
 // mostly meet in one L2 (merged there instead of fetched twice, or written
 // back in parts from two), while all XCDs stay in one region of the buffer.
-// On the 9.47 GB buffer at rate 16, in plain order, in runs of 8 and in runs
-// of 32: decode 3.79, 3.07 and 3.04 ms, encode 2.80, 2.83 and 2.79 ms.  Runs
-// of 128 and 512 are no better.  A partial last group keeps its order.  A
-// bijection on [0, n).
-__device__ __forceinline__ int32_t xcd_grouped(uint32_t i, uint32_t n) {
-  constexpr uint32_t kXcds = 8, kRun = 32, kGroup = kXcds * kRun;
-  if (i >= n / kGroup * kGroup) return (int32_t)i;
-  const uint32_t x = i % kXcds, k = i / kXcds;
-  return (int32_t)((k / kRun) * kGroup + x * kRun + k % kRun);
+// A partial last group keeps its order; k = 0 is the plain order.  A bijection
+// on [0, n).
+__device__ __forceinline__ int32_t xcd_grouped(uint32_t i, uint32_t n, int k) {
+  if (i >> (k + 3) == n >> (k + 3)) return (int32_t)i;
+  const uint32_t x = i & 7, j = i >> 3;
+  return (int32_t)((j >> k << (k + 3)) + (x << k) + (j & ((1u << k) - 1)));
+}
+
+// Runs of 32.  On the 9.47 GB buffer at rate 16, in plain order, in runs of 8
+// and in runs of 32: decode 3.79, 3.07 and 3.04 ms, encode 2.80, 2.83 and 2.79
+// ms.  Runs of 128 and 512 are no better.
+constexpr int kRun32 = 5, kRun8 = 3;
+// The decoder of arrays with other x strides takes runs of 8, unless y is the
+// axis closest in memory.  The blocks along a line of memory are then nbx blocks
+// apart, a few tiles, and runs of 32 keep them on one XCD (90 x 300 x 1000 at
+// rate 8: 138 us, in runs of 8 151).  With z closest they are a level of blocks
+// apart, and with x, at a stride of two or more, a tile's rows fill the lines:
+// longer runs then only crowd one L2 (64 x 512 x 1024 at rate 8 with z closest:
+// 416 us, in runs of 8 356; with an x stride of 2 115 against 108).
+template <bool UNIT>
+__device__ __forceinline__ int decoder_runs(const RegularGeo& geo) {
+  const auto abs64 = [](int64_t s) { return s < 0 ? -s : s; };
+  const int64_t sy = abs64(geo.g.sy);
+  return UNIT || (sy < abs64(geo.g.sx) && sy < abs64(geo.g.sz)) ? kRun32 : kRun8;
+}
+template <bool UNIT>
+__device__ __forceinline__ int decoder_runs(const PlanGeo&) {
+  return kRun32;
 }
 
 // Workgroups cover the tiles of blocks [b_begin, b_end): one tile per
@@ -654,8 +673,11 @@ __device__ __forceinline__ int32_t xcd_grouped(uint32_t i, uint32_t n) {
 // three cards with the XCD-grouped order, from 3.21 to 3.27).  Four wavefronts per SIMD (at rate 16 as many
 // as the LDS slices allow) let instructions of two of them issue together more
 // often than three; five, possible at rate 8, spill and are 5 to 25% slower.
+// Arrays with other x strides (UNIT = false) wait for their scattered lines
+// instead: three, so that fewer lines are in use at once (64 x 512 x 1024 with y
+// closest in memory at rate 8: 117 us, with four 128).
 template <int RATE, bool UNIT, bool PERSIST, class Geo>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k_encode(Geo geo, const float* __restrict__ src,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(UNIT ? 4 : 3, UNIT ? 8 : 3))) void k_encode(Geo geo, const float* __restrict__ src,
                                                 uint64_t* __restrict__ out, int rate_rt,
                                                 int32_t b_begin, int32_t b_end) {
   extern __shared__ uint64_t lds[];
@@ -665,7 +687,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   const int waves = blockDim.x >> 6;
   uint64_t* wlds = lds + (size_t)wave * 64 * lds_stride(rate);
   const int32_t ntiles = tiles_of(b_end - b_begin);
-  int32_t t = (PERSIST ? (int32_t)blockIdx.x : xcd_grouped(blockIdx.x, gridDim.x)) * waves + wave;
+  int32_t t = (PERSIST ? (int32_t)blockIdx.x : xcd_grouped(blockIdx.x, gridDim.x, kRun32)) * waves + wave;
   if (t >= ntiles) return;
   for (;;) {
     const int32_t b0 = b_begin + (t << 6);
@@ -694,7 +716,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   const int waves = blockDim.x >> 6;
   uint64_t* wlds = lds + (size_t)wave * 64 * lds_stride(rate);
   const int32_t ntiles = tiles_of(b_end - b_begin);
-  int32_t t = (PERSIST ? (int32_t)blockIdx.x : xcd_grouped(blockIdx.x, gridDim.x)) * waves + wave;
+  int32_t t = (PERSIST ? (int32_t)blockIdx.x : xcd_grouped(blockIdx.x, gridDim.x, decoder_runs<UNIT>(geo))) * waves + wave;
   if (t >= ntiles) return;
   for (;;) {
     const int32_t b0 = b_begin + (t << 6);
@@ -971,7 +993,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
   const int waves = blockDim.x >> 6;
   uint64_t* slice = lds + (size_t)(wave * 64 + lane) * stride;
   const int32_t ntiles = tiles_of(nblocks);
-  const int32_t t = xcd_grouped(blockIdx.x, gridDim.x) * waves + wave;
+  const int32_t t = xcd_grouped(blockIdx.x, gridDim.x, kRun32) * waves + wave;
   if (t >= ntiles) return;
   const int32_t b0 = t << 6;
   const int nact = nblocks - b0 < 64 ? nblocks - b0 : 64;
