@@ -1725,8 +1725,11 @@ hipError_t launch_plan_decode_var(const PlanDev& p, const uint32_t* in,
   // Four neighbouring tiles per workgroup: the cache lines that they share are
   // completed close in time (precision 16 on the 9.47 GB buffer 2.31 ms, with
   // two 2.52; accuracy 1e-2 on the z->lambda share 74 us, with two 79, with
-  // one 77).
-  constexpr int wg = 256;
+  // one 77).  From cap 24 on only two such workgroups fit a compute unit's LDS,
+  // eight wavefronts where single ones are nine to eleven: precision 16 on 48
+  // levels of that grid 1.33 ms at cap 24, with four tiles 1.64, at cap 32 1.49
+  // and 1.62 (share at full precision, cap 24: 129 and 145 us).
+  const int wg = 3 * lds_bytes(256, cap) <= device_max_lds() ? 256 : 64;
   const int ntiles = tiles_of(nblocks);
   dim3 grid((ntiles + wg / 64 - 1) / (wg / 64)), block(wg);
   size_t shm = lds_bytes(wg, cap);
