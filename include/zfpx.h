@@ -347,9 +347,11 @@ int zfpx_plan_get_config(const zfpx_plan* plan, int op, int rate, int* wg_thread
  * Autotune: time every candidate configuration for `op` and `rate` on this
  * plan with the given buffers (the op is run repeatedly; outputs are
  * overwritten), keep the fastest in the plan and, when cache_path is not
- * NULL, record it in a small text cache keyed by device, op, rate and plan
- * shape (read first: a cached entry skips the timing).  Synchronises the
- * stream; not for hot loops.  best_us receives the chosen mean time.
+ * NULL, record it in a small text cache keyed by device, kernel version, op,
+ * rate and plan shape (read first: a cached entry skips the timing; entries
+ * timed on other versions of the kernels are passed over).  Synchronises the
+ * stream; not for hot loops.  best_us receives the chosen mean time, or -1
+ * where a cached entry was taken.
  */
 int zfpx_autotune(zfpx_plan* plan, int op, int rate, const float* d_src, int64_t src_elems,
                   void* d_stream_buf, size_t stream_bytes, float* d_dst, int64_t dst_elems,

@@ -546,9 +546,9 @@ static std::string tune_key(const zfpx_plan* p, int op, int rate) {
   for (char& ch : arch)
     if (ch == ' ' || ch == ':') ch = '_';
   char buf[256];
-  snprintf(buf, sizeof buf, "%s op%d r%d c%lld b%lld v%lld s%lld", arch.c_str(), op, rate,
-           (long long)p->shape_key[0], (long long)p->shape_key[1], (long long)p->shape_key[2],
-           (long long)p->shape_key[3]);
+  snprintf(buf, sizeof buf, "%s k%d op%d r%d c%lld b%lld v%lld s%lld", arch.c_str(),
+           kTuneVersion, op, rate, (long long)p->shape_key[0], (long long)p->shape_key[1],
+           (long long)p->shape_key[2], (long long)p->shape_key[3]);
   return buf;
 }
 

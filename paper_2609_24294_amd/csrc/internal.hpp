@@ -31,6 +31,11 @@ struct LaunchCfg {
   int grid = 0;
 };
 
+// Part of the tuning cache's key: raised with every change to the fixed-rate
+// kernels or to their launch order, so that a configuration timed on other
+// kernels is not taken for these (entries without a version are older ones).
+constexpr int kTuneVersion = 2;
+
 constexpr int kOpEncode = 0;
 constexpr int kOpDecode = 1;
 
