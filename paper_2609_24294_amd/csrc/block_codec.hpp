@@ -94,10 +94,6 @@ ZFPX_HD float scale_pow2(float f, int e) {
 #endif
 }
 
-ZFPX_HD uint64_t low_mask(int n) {  // n in [0, 64]
-  return n >= 64 ? ~uint64_t(0) : ((uint64_t(1) << n) - 1);
-}
-
 ZFPX_HD int ctz64(uint64_t x) {  // x != 0
   return __builtin_ctzll(x);
 }
@@ -304,7 +300,8 @@ ZFPX_HD void transpose_group(uint64_t* a) {
   transpose_bits64<1, 0x55555555u, INVERT_ODD>(a);
 }
 
-// The whole transpose at once.
+// The whole transpose at once: the same stages, for the mapping probe.  The
+// library runs the two parts apart (the decoder in the other order).
 template <bool INVERT_ODD = false>
 ZFPX_HD void transpose32x2(uint64_t* a) {
   transpose_bytes(a);
@@ -392,17 +389,8 @@ ZFPX_HD uint64_t window_of(const Words3& w, uint32_t pos) {
   return (uint64_t)funnel32(w.w1, w.w0, pos) | ((uint64_t)funnel32(w.w2, w.w1, pos) << 32);
 }
 
-// Make the words of two windows available at this point (an empty asm that
-// reads and writes all six): the six reads are issued first and waited for
-// together, one LDS round trip for both windows.
-ZFPX_HD void pin_words(Words3& a, Words3& b) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("" : "+v"(a.w0), "+v"(a.w1), "+v"(a.w2), "+v"(b.w0), "+v"(b.w1), "+v"(b.w2));
-#else
-  (void)a;
-  (void)b;
-#endif
-}
+// Make the words of a window available at this point (an empty asm that reads
+// and writes all three): the reads are issued first and waited for together.
 ZFPX_HD void pin_words(Words3& a) {
 #if defined(__HIP_DEVICE_COMPILE__)
   asm volatile("" : "+v"(a.w0), "+v"(a.w1), "+v"(a.w2));
@@ -589,7 +577,7 @@ ZFPX_HD uint32_t encode_block(float* v, uint64_t* out, int rate_rt, int maxprec 
   uint32_t pos = 9;
   uint32_t n = 0;    // coefficients significant so far
   uint32_t adv = 1;  // verbatim bits and a group test of 0: n + (n < 64)
-  uint64_t vm = 0;   // low_mask(n)
+  uint64_t vm = 0;   // mask of the low n bits
 #pragma unroll
   for (int g = 3; g >= 0; g--) {
     if (!any_lane(pos < maxbits && (!VAR || 8 * g + 7 >= kmin))) break;
@@ -677,7 +665,7 @@ ZFPX_HD uint64_t parse_groups(uint64_t v, uint64_t& upto) {
 // 64 floats (block-local order).
 //
 // Per bit plane the verbatim bits and the group test are the low n + 1 bits of
-// the window at pos: as a number they pass low_mask(n) exactly when the group
+// the window at pos: as a number they pass 2^n - 1 exactly when the group
 // test is 1.  A plane whose group test is 0 (most of them) is done with that;
 // positions advance by `adv`, kept across planes and updated when n changes.
 // Reads past the budget return the zero slack, which is what a budget that
@@ -710,8 +698,8 @@ ZFPX_HD void decode_block(const uint64_t* in, float* vout, int rate_rt, int maxp
   uint64_t X[32];  // bit planes, then (after the transpose) coefficients s, 32+s
   uint32_t n = 0;     // coefficients significant so far
   uint32_t adv = 1;   // verbatim bits and a group test of 0: n + (n < 64)
-  uint64_t vm = 0;    // low_mask(n)
-  uint64_t vm1 = 1;   // low_mask(min(n + 1, 64))
+  uint64_t vm = 0;    // mask of the low n bits
+  uint64_t vm1 = 1;   // mask of the low min(n + 1, 64) bits
 #pragma unroll
   for (int g = 3; g >= 0; g--) {
     if (!any_lane(pos < maxbits && (!VAR || 8 * g + 7 >= kmin))) {
