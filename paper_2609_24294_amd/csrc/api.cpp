@@ -26,22 +26,14 @@ bool rate_ok(int rate) { return rate >= 1 && rate <= 32; }
 int64_t ceil4(int64_t n) { return (n + 3) / 4; }
 bool aligned(const void* p, uintptr_t a) { return ((uintptr_t)p & (a - 1)) == 0; }
 
-// One tile per wavefront, one wavefront per workgroup: a compute unit then
-// takes the next tile as soon as one of its wavefronts ends, not when two have.
-// With two (128 threads) the 45 x 426 x 853 array encodes 6% slower, the
-// z->lambda share encodes and decodes 1.5 and 2% slower at rate 16 (decode at
-// rate 8: 8%), the small field 2.6%; four gain only where the share decodes at
-// rate 8 (4%) and lose as much elsewhere.
-LaunchCfg default_cfg() { return LaunchCfg{}; }
-
 // Arrays with an x stride other than 1: two wavefronts once the launch has more
 // tiles than the card holds wavefronts (4,096), where neighbouring tiles share
 // the lines of all their rows and are best worked on together (64 x 512 x 1024
 // at rate 8: decoding with z closest in memory takes 356 us, with one wavefront
 // 396; encoding with y closest 117 against 139); below, one (8 x 64 x 128 with
 // z closest: encode 11.1 us, with two 13.0).
-LaunchCfg strided_cfg(bool unit, int64_t nblocks) {
-  LaunchCfg c = default_cfg();
+LaunchCfg regular_cfg(bool unit, int rate, int64_t nblocks) {
+  LaunchCfg c = default_cfg(rate);
   if (!unit && nblocks > 64 * 4096) c.wg = 128;
   return c;
 }
@@ -72,7 +64,7 @@ struct zfpx_plan {
     if (it != cfg.end()) return it->second;
     it = cfg.find({op, 0});
     if (it != cfg.end() && lds_bytes(it->second.wg, rate) <= device_max_lds()) return it->second;
-    return default_cfg();
+    return default_cfg(rate);
   }
 };
 
@@ -134,7 +126,7 @@ int zfpx_encode_fixed_rate(const float* d_in, int64_t nx, int64_t ny, int64_t nz
   if (!d_in || !d_out || !aligned(d_out, 8)) return ZFPX_EINVAL;
   if ((int64_t)out_bytes < nb * 8 * rate) return ZFPX_ENOSPC;
   hipError_t e = launch_regular_encode(g, sx == 1, d_in, (uint64_t*)d_out,
-                                       rate, (int32_t)nb, strided_cfg(sx == 1, nb),
+                                       rate, (int32_t)nb, regular_cfg(sx == 1, rate, nb),
                                        (hipStream_t)stream);
   return e == hipSuccess ? ZFPX_OK : ZFPX_EHIP;
 }
@@ -150,7 +142,7 @@ int zfpx_decode_fixed_rate(const void* d_in, size_t in_bytes, int64_t nx, int64_
   if (!d_in || !d_out || !aligned(d_in, 8)) return ZFPX_EINVAL;
   if ((int64_t)in_bytes < nb * 8 * rate) return ZFPX_ENOSPC;
   hipError_t e = launch_regular_decode(g, sx == 1, (const uint64_t*)d_in,
-                                       d_out, rate, (int32_t)nb, strided_cfg(sx == 1, nb),
+                                       d_out, rate, (int32_t)nb, regular_cfg(sx == 1, rate, nb),
                                        (hipStream_t)stream);
   return e == hipSuccess ? ZFPX_OK : ZFPX_EHIP;
 }
@@ -610,7 +602,7 @@ int zfpx_autotune(zfpx_plan* p, int op, int rate, const float* d_src, int64_t sr
   }
   auto saved = p->cfg;
   double best = 1e300;
-  LaunchCfg best_c = default_cfg();
+  LaunchCfg best_c = default_cfg(rate);
   int st = ZFPX_OK;
   for (const LaunchCfg& c : cands) {
     p->cfg[{op, rate}] = c;

@@ -36,6 +36,9 @@ struct LaunchCfg {
 // kernels is not taken for these (entries without a version are older ones).
 constexpr int kTuneVersion = 2;
 
+// The launch without a configuration of its own (kernels.hip).
+LaunchCfg default_cfg(int rate);
+
 constexpr int kOpEncode = 0;
 constexpr int kOpDecode = 1;
 
@@ -124,6 +127,10 @@ constexpr int kServeWaves = 8;  // wavefronts per workgroup of the device loop
 
 // LDS bytes a workgroup of `wg` threads needs at `rate`.
 size_t lds_bytes(int wg, int rate);
+// Wavefronts that a compute unit holds at `rate` in workgroups of `wg` threads:
+// by its 160 KB of LDS, handed out in steps of 1,280 bytes, at most 16 by the
+// coders' registers.
+int lds_waves(int wg, int rate);
 // Largest LDS per workgroup of the current device (cached).
 size_t device_max_lds();
 int device_cu_count();

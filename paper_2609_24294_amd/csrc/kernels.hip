@@ -1493,6 +1493,28 @@ size_t lds_bytes(int wg, int rate) {
   return (size_t)(wg / 64) * 64 * lds_stride(rate) * sizeof(uint64_t);
 }
 
+int lds_waves(int wg, int rate) {
+  constexpr size_t kPerCu = 160 * 1024, kStep = 1280;
+  const size_t taken = (lds_bytes(wg, rate) + kStep - 1) / kStep * kStep;
+  const int waves = (int)(kPerCu / taken) * (wg / 64);
+  return waves < 16 ? waves : 16;
+}
+
+// One tile per wavefront, one wavefront per workgroup: a compute unit then
+// takes the next tile as soon as one of its wavefronts ends, not when two have.
+// With two (128 threads) the 45 x 426 x 853 array encodes 6% slower, the
+// z->lambda share encodes and decodes 5 and 2% slower at rate 16, the small
+// field 2.6%; four gain only where the share decodes at rate 8 and lose as much
+// elsewhere.  At rates 28 and 29 LDS holds ten wavefronts in pairs and nine
+// singly: two there (the share at rate 28 encodes in 107 us and decodes in 149,
+// with one 109 and 154; 2,400 tiles of Fourier-space chunks, one round of ten
+// but not of nine, decode in 28 us, with one 36).
+LaunchCfg default_cfg(int rate) {
+  LaunchCfg c;
+  c.wg = lds_waves(128, rate) > lds_waves(64, rate) ? 128 : 64;
+  return c;
+}
+
 static int g_cus = -1;
 static size_t g_max_lds = 0;
 
@@ -1688,7 +1710,7 @@ hipError_t launch_plan_encode_var(const PlanDev& p, const float* src, uint32_t* 
                                   uint32_t* stage, uint32_t* tile_count, int cap,
                                   int32_t nblocks, int maxprec, int minexp, hipStream_t s) {
   if (nblocks <= 0) return hipSuccess;
-  constexpr int wg = 64;  // as for fixed rate (with 128 the share takes 1% longer)
+  const int wg = default_cfg(cap).wg;  // with 128 at cap 16 the share takes 1% longer
   const int ntiles = tiles_of(nblocks);
   dim3 grid((ntiles + wg / 64 - 1) / (wg / 64)), block(wg);
   size_t shm = lds_bytes(wg, cap);
@@ -1726,10 +1748,11 @@ hipError_t launch_plan_decode_var(const PlanDev& p, const uint32_t* in,
   // completed close in time (precision 16 on the 9.47 GB buffer 2.31 ms, with
   // two 2.52; accuracy 1e-2 on the z->lambda share 74 us, with two 79, with
   // one 77).  From cap 24 on only two such workgroups fit a compute unit's LDS,
-  // eight wavefronts where single ones are nine to eleven: precision 16 on 48
-  // levels of that grid 1.33 ms at cap 24, with four tiles 1.64, at cap 32 1.49
-  // and 1.62 (share at full precision, cap 24: 129 and 145 us).
-  const int wg = 3 * lds_bytes(256, cap) <= device_max_lds() ? 256 : 64;
+  // eight wavefronts, and the tiles go as in fixed rate, where nine to eleven
+  // fit: precision 16 on 48 levels of that grid 1.33 ms at cap 24, with four
+  // tiles 1.64, at cap 32 1.49 and 1.62 (share at full precision, cap 24: 129
+  // and 145 us).
+  const int wg = lds_waves(256, cap) >= 12 ? 256 : default_cfg(cap).wg;
   const int ntiles = tiles_of(nblocks);
   dim3 grid((ntiles + wg / 64 - 1) / (wg / 64)), block(wg);
   size_t shm = lds_bytes(wg, cap);
