@@ -668,11 +668,14 @@ __device__ __forceinline__ int decoder_runs(const PlanGeo&) {
 // Workgroups cover the tiles of blocks [b_begin, b_end): one tile per
 // wavefront, or (PERSIST) a grid-stride loop over tiles.
 // Bound by vector instruction issue (93% of the issue slots taken on the
-// 9.47 GB buffer at rate 16; 2,916 vector instructions per tile, where a loop
+// 9.47 GB buffer at rate 16; 2,904 vector instructions per tile, where a loop
 // over groups wherever coefficient 63 is reached took 3,407: 2.69 to 2.82 ms on
-// three cards with the XCD-grouped order, from 3.21 to 3.27).  Four wavefronts per SIMD (at rate 16 as many
-// as the LDS slices allow) let instructions of two of them issue together more
-// often than three; five, possible at rate 8, spill and are 5 to 25% slower.
+// four cards with the XCD-grouped order, from 3.21 to 3.30, timed alone).  Four
+// wavefronts per SIMD (at rate 16 as many as the LDS slices allow) let
+// instructions of two of them issue together more often than three; the plan
+// encoders made to run at five, possible at rate 8, spill and are 5 to 25%
+// slower (the one-tile encoders of regular arrays need 96 registers and do run
+// at five where the rate leaves LDS for it).
 // Arrays with other x strides (UNIT = false) wait for their scattered lines
 // instead: three, so that fewer lines are in use at once (64 x 512 x 1024 with y
 // closest in memory at rate 8: 117 us, with four 128).
@@ -700,9 +703,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(UNIT ? 4 : 
   }
 }
 
-// Bound by vector instruction issue (87% of the slots on the 9.47 GB buffer at
-// rate 16; 2,825 vector instructions per tile and 2.93 to 3.06 ms on three
-// cards, from 3,380 and 3.51) with its writes close behind (16 row pieces of 1 KB per tile).  Four
+// Bound by its writes (16 row pieces of 1 KB per tile) and by vector
+// instruction issue at once: on the 9.47 GB buffer at rate 16 it takes 2.93 to
+// 3.09 ms on four cards, from 3.51, timed alone, and a copy in its pattern at the
+// same occupancy 2.98; 90% of the issue slots are taken (2,968 vector
+// instructions per tile there; 2,825 on the bench's field, from 3,380).  Four
 // wavefronts per SIMD hold the block without spilling; three are a fifth
 // slower.
 template <int RATE, bool UNIT, bool PERSIST, class Geo>
@@ -738,8 +743,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void k
 // size, so encoding runs in stages that never wait on each other's progress:
 // (1) each wavefront codes its 64-block tile as in fixed rate and writes the
 // tile's words, compacted, to its own staging slot of 64 * 2 * cap words,
-// plus the per-block counts and the tile's count; (2) a chunked scan (three
-// short launches) turns the tile counts into tile offsets; (3) each wavefront
+// plus the per-block counts and the tile's count; (2) a chunked scan (one short
+// launch, or three beyond kScanFew chunks) turns the tile counts into tile
+// offsets; (3) each wavefront
 // copies its tile's words from the staging slot to the tile's offset.  The words, which
 // are the bulk of the traffic, are stored as contiguous 256-byte stretches
 // per wavefront instruction in both (1) and (3).
@@ -807,8 +813,9 @@ __global__ __launch_bounds__(256) void k_encode_var(Geo geo, const float* __rest
   }
 }
 
-// Tile offsets = exclusive prefix sum of the tile counts, in three launches
-// over chunks of kScanChunk counts (8 per thread of a 1024-thread group):
+// Tile offsets = exclusive prefix sum of the tile counts, over chunks of
+// kScanChunk counts (8 per thread of a 1024-thread group), in one launch for few
+// chunks (k_var_scan_few below) or in three:
 // (1) each chunk's sum, parked in tile_off at the chunk's first position;
 // (2) one group scans the chunk sums in place into chunk bases and writes the
 // total at tile_off[ntiles]; (3) each chunk reads its base, then scans its
