@@ -41,6 +41,7 @@ __device__ __forceinline__ T uniform_load(const T* p, int64_t i) {
 }
 
 struct PlanGeo {
+  static constexpr bool kStreamLoads = true;
   PlanDev p;
   // True (the same on every lane) when blocks b0 .. b0 + nact - 1 lie in one
   // run; r then describes it.
@@ -366,7 +367,14 @@ __device__ __forceinline__ BlockView run_block(const RunView& r, int32_t x0) {
 }
 
 // Block b of a one-run tile.  If every block of the tile is whole: sixteen
-// 16-byte pieces at a scalar row address plus the lane's x offset.
+// 16-byte pieces at a scalar row address plus the lane's x offset.  STREAM: with
+// streaming (non-temporal) loads, for a plan's send buffer, which is read once.
+// A regular array is a field that its owner may go on using: ordinary loads
+// leave it in the caches (64 x 1024 x 1024 at rate 8, encoded and then read for
+// its maximum: 111 us, streaming 138; the encoder alone, nothing of the array in
+// the caches before, 65 and 64; 64 x 512 x 256 encoded again and again 12.4 and
+// 13.9).
+template <bool STREAM>
 __device__ __forceinline__ void gather_run(const float* __restrict__ src, const RunView& r,
                                            int32_t b, float* val) {
   const int32_t x0 = 4 * (b - r.block0);
@@ -376,9 +384,8 @@ __device__ __forceinline__ void gather_run(const float* __restrict__ src, const 
 #pragma unroll
       for (int dy = 0; dy < 4; dy++) {
         const float* row = src + (r.rbase[dy] + dz * r.lstride);
-        // read once: a streaming (non-temporal) load
-        const f32x4_row f =
-            __builtin_nontemporal_load(reinterpret_cast<const f32x4_row*>(row + (uint32_t)x0));
+        const f32x4_row* piece = reinterpret_cast<const f32x4_row*>(row + (uint32_t)x0);
+        const f32x4_row f = STREAM ? __builtin_nontemporal_load(piece) : *piece;
         float* o = val + 16 * dz + 4 * dy;
         o[0] = f.x;
         o[1] = f.y;
@@ -593,7 +600,7 @@ __device__ __forceinline__ void encode_tile(const Geo& geo, const float* __restr
   if (lane < nact) {
     float val[64];
     if (uniform) {
-      gather_run(src, run, b0 + lane, val);
+      gather_run<Geo::kStreamLoads>(src, run, b0 + lane, val);
     } else {
       BlockView v;
       geo.locate_tile(b0, lane, nact, v);

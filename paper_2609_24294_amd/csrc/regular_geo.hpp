@@ -55,6 +55,7 @@ inline int64_t regular_blocks(int64_t nx, int64_t ny, int64_t nz) {
 }
 
 struct RegularGeo {
+  static constexpr bool kStreamLoads = false;
   RegularDev g;
   // Positions within a row are 32-bit, a row may be longer (nx up to four
   // times the number of blocks, 2^33): they count from the last multiple of
